@@ -1,0 +1,17 @@
+// Instantiations of the 16-row-tile ring kernel (xcorr16.hpp) for any N, with
+// 15 tiles loaded in 16-byte chunks.
+// (Several translation units so that they compile in parallel.)
+#include "x16_ragged.hpp"
+
+namespace xeng {
+namespace x16 {
+namespace {
+
+const KernelInfo kTable[1] = {ragged_info<15, LD_CHUNK>()};
+
+}  // namespace
+}  // namespace x16
+
+const KernelInfo* x16_ragged_e(int nt) { return nt >= 15 && nt <= 15 ? &x16::kTable[nt - 15] : nullptr; }
+
+}  // namespace xeng

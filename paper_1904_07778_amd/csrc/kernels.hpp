@@ -15,6 +15,8 @@ struct KernelInfo {
   int64_t max_row_bytes; // largest time row F*N the kernel addresses (0: any)
   int tile_rows;         // rows of its tiles: 16 or 32
   LaunchFn launch;
+  int load_unit = 0;     // ragged kernels: bytes that every row offset must share
+                         // (rows are taken in phases where F*N is no multiple); 0: none
 };
 
 // Staging kernel (any N), by 16-row tile count nt = ceil(N/16), 1..16.
@@ -48,6 +50,68 @@ inline const KernelInfo* x16_kernel(int n) {
   if (!k) k = x16_kernel_e(n);
   if (!k) k = x16_kernel_f(n);
   return k;
+}
+// The same kernel for any other N, by tile count: _a .. _f load 16-byte
+// chunks (1 .. 16 tiles), _g .. _k 4-byte units (8 .. 16 tiles).
+const KernelInfo* x16_ragged_a(int nt);
+const KernelInfo* x16_ragged_b(int nt);
+const KernelInfo* x16_ragged_c(int nt);
+const KernelInfo* x16_ragged_d(int nt);
+const KernelInfo* x16_ragged_e(int nt);
+const KernelInfo* x16_ragged_f(int nt);
+const KernelInfo* x16_ragged_g(int nt);
+const KernelInfo* x16_ragged_h(int nt);
+const KernelInfo* x16_ragged_i(int nt);
+const KernelInfo* x16_ragged_j(int nt);
+const KernelInfo* x16_ragged_k(int nt);
+constexpr int gcd(int64_t a, int b) {
+  while (b) {
+    const int r = (int)(a % b);
+    a = b;
+    b = r;
+  }
+  return (int)a;
+}
+constexpr int ragged_tiles(int n, int unit) { return (n + unit - gcd(n, unit) + 15) / 16; }
+// The kernel for rows of f channels of n inputs.  The tiles start at the
+// whole load unit that holds a channel's first byte, up to unit - gcd(n, unit)
+// bytes before it, so they must cover that many positions more than n.  From
+// 8 tiles up, chunks are taken where they need no tile more than n alone and
+// every row starts on a chunk: at F = 1024, T = 4096 they are 3-13% faster
+// there (N = 200: 299 against 319 us; a chunk load moves 1 KB, a dword load
+// one row of at most 256 bytes).  With a tile more they are slower (N = 230:
+// 461 against 388), and where rows do not start on a chunk they take up to
+// 16 phases against 4 (N = 113, F = 933: 1389 against 352 us).  Below 8
+// tiles the array is bound by memory and a tile more costs little.  N = 255
+// fits neither (its 258 positions are 17 tiles).
+inline const KernelInfo* x16_any_kernel(int n, int64_t f) {
+  if (n % 16 == 0) return x16_kernel(n);
+  const KernelInfo* k = nullptr;
+  int nt = ragged_tiles(n, 16);
+  if (nt >= 8 && (nt > (n + 15) / 16 || f * n % 16 != 0)) {
+    nt = ragged_tiles(n, 4);
+    if (nt > 16) return nullptr;
+    if (nt >= 8) {
+      k = x16_ragged_g(nt);
+      if (!k) k = x16_ragged_h(nt);
+      if (!k) k = x16_ragged_i(nt);
+      if (!k) k = x16_ragged_j(nt);
+      if (!k) k = x16_ragged_k(nt);
+      return k;
+    }
+    nt = ragged_tiles(n, 16);
+  }
+  k = x16_ragged_a(nt);
+  if (!k) k = x16_ragged_b(nt);
+  if (!k) k = x16_ragged_c(nt);
+  if (!k) k = x16_ragged_d(nt);
+  if (!k) k = x16_ragged_e(nt);
+  if (!k) k = x16_ragged_f(nt);
+  return k;
+}
+// Phases of time rows of a ragged kernel for rows of row_bytes = F*N.
+inline int row_phases(const KernelInfo* k, int64_t row_bytes) {
+  return k->load_unit ? k->load_unit / gcd(row_bytes, k->load_unit) : 1;
 }
 
 // Copy n[k] int2 values (re, im) from acc[k] to dst[k] for k < count; a

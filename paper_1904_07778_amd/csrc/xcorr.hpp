@@ -171,6 +171,7 @@ struct Args {
   int F, N;
   int64_t t_chunk;   // samples per workgroup along time (multiple of KS)
   int mode;          // EpiMode
+  int period;        // ragged 16-row kernel: phases of time rows (1: one)
 };
 
 // How a launch leaves its sums in the accumulator.

@@ -1,5 +1,5 @@
 // xcorr16.hpp - gfx950 X-engine kernel on 16-row tiles (v_mfma_i32_16x16x64_i8),
-// N a multiple of 16 up to 256.
+// N up to 256 (not a multiple of 16: see LoadMode; all but 255).
 //
 // Result (paper Sec. 2 and Sec. 2.2): for each channel f of the grid and each
 // pair 0 <= j <= i < N, the exact int32 sum over the launch's time range of
@@ -63,6 +63,30 @@ constexpr int TILE_ROWS = 16;
 // the kernel needs 32 KPS F N < 2^32 bytes.
 constexpr int64_t MAX_ROW_BYTES = ((int64_t)1 << 32) / (32 * KPS_DEFAULT) - 1;
 constexpr int MAX_UNITS_PER_WAVE = 60;
+
+// How a stage's rows are loaded, and what N means to the templates below.
+//   LD_EXACT   N inputs, a multiple of 16: every channel starts on a 16-byte
+//              boundary of the row.
+//   LD_CHUNK   up to N = 16 NT inputs, any number (a.N).  A channel's bytes
+//              start s = (offset mod 16) bytes into a 16-byte chunk; the
+//              loads take the whole chunks that hold them, and the tiles
+//              cover the s + a.N positions from the first chunk's start.  The
+//              bytes of neighbouring channels in the first and last chunk are
+//              correlated too and never written: an output depends on its
+//              own two inputs alone.  So nothing is shifted or masked in the
+//              main loop; s only enters the baseline index of the epilogue.
+//   LD_DWORD   the same in 4-byte units (s < 4), one wave-wide load per row,
+//              for N whose s + N does not fit the tiles in 16-byte units.
+// s must be the same for every row a workgroup sums.  Where the row stride
+// F N is no multiple of the unit, the rows are taken in a.period interleaved
+// phases (row t belongs to phase t % period), one workgroup each, and the
+// phases meet in the accumulator by atomic adds.  The staging kernel, which
+// such N used to take, loads single bytes or dwords to registers, transposes
+// and unpacks them there and writes the operands to LDS: at F = 1024, T =
+// 4096, N = 250 took 3091 us there and takes 472 here (N = 200: 882 and 299;
+// N = 40, T = 8192: 202 and 75).
+enum LoadMode : int { LD_EXACT = 0, LD_CHUNK = 1, LD_DWORD = 2 };
+constexpr int load_unit(int ld) { return ld == LD_DWORD ? 4 : 16; }
 
 template <int B, int E, typename F>
 __device__ __forceinline__ void sfor(F&& f) {
@@ -148,24 +172,27 @@ struct Plan16 {
   }
 };
 
-template <int N, int CPW, int S, int KPS>
+template <int N, int CPW, int S, int KPS, int LD = LD_EXACT>
 struct Shape {
   static constexpr int STAGE_T = 32 * KPS;            // time samples per ring stage (KPS 32-sample steps)
   static constexpr int NT = tiles(N);
-  static constexpr int W = waves_per_channel(NT);
+  static constexpr int W = LD == LD_DWORD ? 4 : waves_per_channel(NT);
   static constexpr int THREADS = 64 * W * CPW;
   static constexpr int RPC = CPW * N / 16;            // 16-byte chunks of data per time row
   static constexpr int RPP = RPC | 1;                 // odd row pitch in chunks
   static constexpr int STAGE_BYTES = STAGE_T * RPP * 16;
   static constexpr int LOADS = STAGE_BYTES / 1024;    // wave-wide 1 KB loads per stage (= RPP)
   static constexpr int WAVES = W * CPW;
+  static constexpr int ROWS_PER_WAVE = STAGE_T / WAVES;  // LD_DWORD: one load per row, an equal run per wave
   static constexpr int LPW_MAX = (LOADS + WAVES - 1) / WAVES;
   static constexpr int LPW_MIN = LOADS / WAVES;
   static constexpr int DIAG_BYTES = CPW * N * 4;
   static constexpr int LDS_BYTES = S * STAGE_BYTES > DIAG_BYTES ? S * STAGE_BYTES : DIAG_BYTES;
   static_assert(supported(N), "N must be a multiple of 16 up to 256");
   static_assert(LOADS * 1024 == STAGE_BYTES, "a stage is whole 1 KB loads");
-  static_assert(S >= 3 && (S - 2) * (CPW == 1 ? (LOADS + 1) / 2 : LPW_MAX) < 64, "ring depth");
+  static_assert(S >= 3 && (S - 2) * (LD == LD_DWORD ? ROWS_PER_WAVE : CPW == 1 ? (LOADS + 1) / 2 : LPW_MAX) < 64,
+                "ring depth");
+  static_assert(LD != LD_DWORD || RPC * 4 <= 64, "a row is at most one wave-wide load of dwords");
   static_assert(KPS >= 2 && KPS % 2 == 0, "an even number of steps per stage");
   static_assert(WAVES == 4, "four waves per workgroup");
 };
@@ -201,6 +228,15 @@ __device__ __forceinline__ void buf_dma16(v4i rsrc, uint32_t voff, uint32_t lds_
       : "v"(voff), "s"(rsrc), "s"(lds_base)
       : "memory", "m0");
 }
+// The same with 4 bytes per lane: a wave-wide 256-byte load.
+__device__ __forceinline__ void buf_dma4(v4i rsrc, uint32_t voff, uint32_t lds_base) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "buffer_load_dword %0, %1, 0 offen lds"
+      :
+      : "v"(voff), "s"(rsrc), "s"(lds_base)
+      : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
@@ -222,14 +258,26 @@ __device__ __forceinline__ int32_t acc_read(const v4i& t, int v) {
 // Add one wave's tiles into the accumulator of channel f.  16x16 result
 // layout: lane l, register v hold row 4(l/16) + v, column l%16; the 16 lanes
 // of a group write 16 consecutive baselines of one row.  drow: the diagonal
-// values D_n of this channel (LDS).
-template <int N, int W, int WC, int MODE, int NU>
+// values D_n of this channel (LDS).  Ragged loads: position p of the tiles is
+// input p - s; positions outside 0 .. a.N - 1 are dropped.
+template <int N, int W, int WC, int MODE, int LD, int NU>
 __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v4i (&acc)[NU],
-                                         const int32_t* drow) {
+                                         const int32_t* drow, int s) {
   constexpr int NT = tiles(N);
   constexpr Plan16<NT, W> plan{};
   constexpr bool QC = plan.qcol[WC];
-  constexpr int nbl = N * (N + 1) / 2;
+  const int nin = LD == LD_EXACT ? N : a.N;
+  const int nbl = nin * (nin + 1) / 2;
+  // whether the site of tile pair (I, J) at input i, j is a baseline: the
+  // first tile may hold positions below 0, the last two positions past a.N
+  auto baseline = [&](auto I, auto J, int i, int j) {
+    bool ok = decltype(J)::value < decltype(I)::value || j <= i;
+    if constexpr (LD != LD_EXACT) {
+      if constexpr (decltype(J)::value == 0) ok = ok && j >= 0;
+      if constexpr (decltype(I)::value >= NT - 2) ok = ok && i < nin;
+    }
+    return ok;
+  };
   int32_t* accf = a.acc + (int64_t)f * nbl * 2;
   const int n = lane & 15;
   const int mb = 4 * (lane >> 4);
@@ -251,11 +299,11 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
                               plan.uIm[WC][un];
         constexpr bool DONE = IM && u > 0 && plan.uI[WC][up] == I && plan.uJ[WC][up] == J && !plan.uIm[WC][up];
         if constexpr (!DONE) {
-          const int j = 16 * J + n;
-          const int i = 16 * I + mb + v;
-          if (J < I || j <= i)
+          const int j = 16 * J + n - s;
+          const int i = 16 * I + mb + v - s;
+          if (baseline(std::integral_constant<int, I>{}, std::integral_constant<int, J>{}, i, j))
             body(std::integral_constant<bool, PAIR>{}, std::integral_constant<int, IM>{},
-                 accf + (i * (i + 1) / 2 + j) * 2, j, un);
+                 accf + (i * (i + 1) / 2 + j) * 2, 16 * J + n, un);
         }
       };
       sfor<u0, u1>([&](auto u) {
@@ -271,12 +319,12 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
       sfor<u0, u1>([&](auto u) {
         constexpr int I = plan.uI[WC][u];
         sfor<0, 4>([&](auto v) {
-          site(u, v, [&](auto pair, auto im, int32_t* dst, int j, int un) {
+          site(u, v, [&](auto pair, auto im, int32_t* dst, int jp, int un) {
             auto im_of = [&](int32_t x) {
               if constexpr (QC)
                 return (drow[16 * I + mb + (int)v] - x) >> 8;
               else
-                return (x - drow[j]) >> 8;
+                return (x - drow[jp]) >> 8;
             };
             const int32_t x = acc_read(acc[u], v);
             if constexpr (pair.value) {
@@ -300,18 +348,18 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
                           plan.uIm[WC][un];
     constexpr bool DONE = IM && u > 0 && plan.uI[WC][up] == I && plan.uJ[WC][up] == J && !plan.uIm[WC][up];
     if constexpr (!DONE) {
-      const int j = 16 * J + n;
+      const int j = 16 * J + n - s;
       int32_t dj = 0;
       v4i di = v4i{0, 0, 0, 0};
       if constexpr (IM || PAIR) {
         if constexpr (QC)
           di = *reinterpret_cast<const v4i*>(drow + 16 * I + mb);
         else
-          dj = drow[j];
+          dj = drow[16 * J + n];
       }
       sfor<0, 4>([&](auto v) {
-        const int i = 16 * I + mb + v;
-        if (J < I || j <= i) {
+        const int i = 16 * I + mb + v - s;
+        if (baseline(std::integral_constant<int, I>{}, std::integral_constant<int, J>{}, i, j)) {
           int32_t* dst = accf + (i * (i + 1) / 2 + j) * 2;
           auto im_of = [&](int32_t x) { return QC ? (di[(int)v] - x) >> 8 : (x - dj) >> 8; };
           const int32_t x = acc_read(acc[u], v);
@@ -342,9 +390,10 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
 // chunk `tchunk` (samples tchunk*t_chunk ..) of the call described by a.
 // tid is threadIdx.x (passed in so that a persistent caller can keep the
 // per-lane set-up from being hoisted out of its item loop).
-template <int N, int CPW, int S, int KPS, int WC>
+template <int N, int CPW, int S, int KPS, int LD, int WC>
 __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group, int tchunk, int tid) {
-  using C = Shape<N, CPW, S, KPS>;
+  using C = Shape<N, CPW, S, KPS, LD>;
+  constexpr int UNIT = load_unit(LD);
   constexpr int STAGE_T = C::STAGE_T;
   constexpr int NT = C::NT, W = C::W;
   constexpr Plan16<NT, W> plan{};
@@ -355,12 +404,20 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = wave / W;
   const int f0 = group * CPW;
-  const int64_t t_begin = (int64_t)tchunk * a.t_chunk;
-  const int64_t t_end = min(a.T, t_begin + a.t_chunk);
+  // ragged: chunk tchunk / period of phase tchunk % period (rows phase, phase + period, ..)
+  const int period = LD == LD_EXACT ? 1 : a.period;
+  const int phase = LD == LD_EXACT ? 0 : tchunk % period;
+  const int64_t rows_all = LD == LD_EXACT ? a.T : (a.T - phase + period - 1) / period;
+  const int64_t t_begin = (int64_t)(LD == LD_EXACT ? tchunk : tchunk / period) * a.t_chunk;
+  const int64_t t_end = min(rows_all, t_begin + a.t_chunk);
   if (t_end <= t_begin) return;  // uniform over the workgroup
   const int nt = (int)(t_end - t_begin);
   const int nstages = (nt + STAGE_T - 1) / STAGE_T;
-  const uint32_t rs32 = (uint32_t)((int64_t)a.F * N);  // one time row; 64 F N < 2^32
+  const int nin = LD == LD_EXACT ? N : a.N;
+  const uint32_t rs32 = (uint32_t)((int64_t)period * a.F * nin);  // from row to row of the phase; 64 rs32 < 2^32
+  // offset of the phase's first row in its load unit; rs32 is a whole number of units
+  const uint64_t phase_off = LD == LD_EXACT ? 0 : (uint64_t)phase * (uint32_t)(a.F * nin);
+  const uint32_t sub = (uint32_t)phase_off & (UNIT - 1);
   const int nch_valid = min(CPW, a.F - f0);             // the last group may be short of channels
 
   // ---- producer: the wave-wide 1 KB loads q = 0 .. LOADS-1 of every stage.
@@ -371,7 +428,7 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
   constexpr int NLW = ONE ? 2 : C::WAVES;                 // loader waves
   constexpr int LR = ONE ? plan.lrank[WC] : 0;            // this wave's rank (one channel)
   constexpr int LW = ONE ? (LR < 0 ? 0 : (C::LOADS - LR + NLW - 1) / NLW) : 0;
-  constexpr int LMAX = ONE ? (C::LOADS + NLW - 1) / NLW : C::LPW_MAX;
+  constexpr int LMAX = LD == LD_DWORD ? 1 : ONE ? (C::LOADS + NLW - 1) / NLW : C::LPW_MAX;
   const int rank = ONE ? LR : wave;
   const int my_loads = ONE ? LW : (C::LOADS - wave + C::WAVES - 1) / C::WAVES;
   uint32_t voff[LMAX];
@@ -385,10 +442,21 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
     int ch = p / (N / 16);
     const int kc = p % (N / 16);
     if (ch >= nch_valid) ch = nch_valid - 1;              // channels past F: dropped later
-    voff[k] = (uint32_t)t * rs32 + (uint32_t)((f0 + ch) * N + 16 * kc);
+    if constexpr (LD == LD_EXACT) {
+      voff[k] = (uint32_t)t * rs32 + (uint32_t)((f0 + ch) * N + 16 * kc);
+    } else if constexpr (LD == LD_CHUNK) {
+      const uint32_t first = sub + (uint32_t)(f0 + ch) * (uint32_t)nin;  // of the channel's bytes
+      const uint32_t off = (first & ~15u) + 16u * (uint32_t)kc;
+      voff[k] = (uint32_t)t * rs32 + min(off, (first + nin - 1) & ~15u);  // chunks past its last: its last
+    } else {
+      // lane l takes dword l of the row's tiles; load k adds k rows
+      const uint32_t first = sub + (uint32_t)f0 * (uint32_t)nin;
+      voff[k] = (uint32_t)(wave * C::ROWS_PER_WAVE) * rs32 +
+                min((first & ~3u) + 4u * (uint32_t)lane, (first + nin - 1) & ~3u);
+    }
   }
   const uint32_t ring_base = __builtin_amdgcn_readfirstlane(lds_addr(lds));
-  const uint64_t vbase = (uint64_t)(uintptr_t)a.v + (uint64_t)t_begin * rs32;
+  const uint64_t vbase = (uint64_t)(uintptr_t)a.v + (uint64_t)t_begin * rs32 + (phase_off - sub);
   // Stages past the last are issued too, with no valid bytes: every stage
   // then counts the same loads per wave (uniform vmcnt waits) and the loop
   // needs no tail.  Their zeros land in slots that are no longer read, and
@@ -407,6 +475,14 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
     rsrc[2] = __builtin_amdgcn_readfirstlane((int)((uint32_t)rows * rs32));
     rsrc[3] = 0x00020000;  // raw buffer, 32-bit data format
     const uint32_t base = ring_base + (uint32_t)((st % S) * C::STAGE_BYTES);
+    if constexpr (LD == LD_DWORD) {
+      if (C::RPC * 4 == 64 || lane < C::RPC * 4) {
+#pragma unroll
+        for (int k = 0; k < C::ROWS_PER_WAVE; ++k)
+          buf_dma4(rsrc, voff[0] + (uint32_t)k * rs32, base + (wave * C::ROWS_PER_WAVE + k) * (C::RPP * 16));
+      }
+      return;
+    }
 #pragma unroll
     for (int k = 0; k < LMAX; ++k) {
       if constexpr (ONE) {
@@ -432,7 +508,9 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
   // rows past the end are zeroed here so the readers need no masks.
   auto enter_stage = [&](int st) {
     // the S-2 stages after st stay in flight
-    if constexpr (ONE)
+    if constexpr (LD == LD_DWORD)
+      wait_vmcnt<(S - 2) * C::ROWS_PER_WAVE>();
+    else if constexpr (ONE)
       wait_vmcnt<(S - 2) * LW>();
     else if (my_loads == C::LPW_MAX)
       wait_vmcnt<(S - 2) * C::LPW_MAX>();
@@ -622,22 +700,23 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
   const int f = f0 + c;
   if (f >= a.F) return;
   const int32_t* drow = diag + c * N;
+  const int s = LD == LD_EXACT ? 0 : (int)((sub + (uint32_t)f * (uint32_t)nin) & (UNIT - 1));
   if (a.mode == EPI_ATOMIC)
-    x16::epilogue<N, W, WC, EPI_ATOMIC>(a, f, lane, acc, drow);
+    x16::epilogue<N, W, WC, EPI_ATOMIC, LD>(a, f, lane, acc, drow, s);
   else if (a.mode == EPI_ADD)
-    x16::epilogue<N, W, WC, EPI_ADD>(a, f, lane, acc, drow);
+    x16::epilogue<N, W, WC, EPI_ADD, LD>(a, f, lane, acc, drow, s);
   else
-    x16::epilogue<N, W, WC, EPI_STORE>(a, f, lane, acc, drow);
+    x16::epilogue<N, W, WC, EPI_STORE, LD>(a, f, lane, acc, drow, s);
 }
 
-template <int N, int CPW, int S, int KPS, int WC>
+template <int N, int CPW, int S, int KPS, int LD, int WC>
 __device__ __forceinline__ void dispatch(int wc, const Args& a, uint8_t* lds, int group, int tchunk,
                                          int tid) {
-  if constexpr (WC < Shape<N, CPW, S, KPS>::W) {
+  if constexpr (WC < Shape<N, CPW, S, KPS, LD>::W) {
     if (wc == WC)
-      x16::wave_main<N, CPW, S, KPS, WC>(a, lds, group, tchunk, tid);
+      x16::wave_main<N, CPW, S, KPS, LD, WC>(a, lds, group, tchunk, tid);
     else
-      x16::dispatch<N, CPW, S, KPS, WC + 1>(wc, a, lds, group, tchunk, tid);
+      x16::dispatch<N, CPW, S, KPS, LD, WC + 1>(wc, a, lds, group, tchunk, tid);
   }
 }
 
@@ -646,15 +725,15 @@ template <int N, int KPS>
 __device__ __forceinline__ void run_item(const Args& a, uint8_t* lds, int group, int tchunk, int tid) {
   constexpr int CPW = cpw_for(N), S = stages_for(N, KPS);
   const int wc = __builtin_amdgcn_readfirstlane(tid >> 6) % Shape<N, CPW, S, KPS>::W;
-  x16::dispatch<N, CPW, S, KPS, 0>(wc, a, lds, group, tchunk, tid);
+  x16::dispatch<N, CPW, S, KPS, LD_EXACT, 0>(wc, a, lds, group, tchunk, tid);
 }
 
-template <int N, int CPW, int S, int KPS>
-__global__ __launch_bounds__((Shape<N, CPW, S, KPS>::THREADS))
+template <int N, int CPW, int S, int KPS, int LD = LD_EXACT>
+__global__ __launch_bounds__((Shape<N, CPW, S, KPS, LD>::THREADS))
 __attribute__((amdgpu_waves_per_eu(1))) void kernel(Args a) {
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[Shape<N, CPW, S, KPS>::LDS_BYTES];
-  const int wc = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % Shape<N, CPW, S, KPS>::W;
-  x16::dispatch<N, CPW, S, KPS, 0>(wc, a, lds, xcd_group(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x);
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[Shape<N, CPW, S, KPS, LD>::LDS_BYTES];
+  const int wc = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % Shape<N, CPW, S, KPS, LD>::W;
+  x16::dispatch<N, CPW, S, KPS, LD, 0>(wc, a, lds, xcd_group(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x);
 }
 
 }  // namespace x16

@@ -52,18 +52,19 @@ struct ArrayState {
 // whole process (xeng_tune_cache_save / _load write and read it as text).
 enum KernelKind { KIND_X16 = 0, KIND_X32 = 1, KIND_STAGE = 2 };
 
-const KernelInfo* kernel_of(int kind, int32_t n) {
+const KernelInfo* kernel_of(int kind, const xeng_array_desc& d) {
+  const int32_t n = d.n_inputs;
   switch (kind) {
-    case KIND_X16: return xeng::x16_kernel(n);
+    case KIND_X16: return xeng::x16_any_kernel(n, d.n_chans);
     case KIND_X32: return xeng::x32_kernel(n);
     case KIND_STAGE: return xeng::stage_kernel((n + 15) / 16);
     default: return nullptr;
   }
 }
 
-int kind_of(const KernelInfo* k, int32_t n) {
-  if (k == xeng::x16_kernel(n)) return KIND_X16;
-  if (k == xeng::x32_kernel(n)) return KIND_X32;
+int kind_of(const KernelInfo* k, const xeng_array_desc& d) {
+  if (k == xeng::x16_any_kernel(d.n_inputs, d.n_chans)) return KIND_X16;
+  if (k == xeng::x32_kernel(d.n_inputs)) return KIND_X32;
   return KIND_STAGE;
 }
 
@@ -139,12 +140,14 @@ void grid_for(const xeng_plan_t* p, const ArrayState& s, int64_t T, dim3& grid, 
               int& mode) {
   const int ngroups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
   const int64_t target = (int64_t)s.split * p->n_cu;
-  int64_t ts = (target + ngroups - 1) / ngroups;
-  ts = std::max<int64_t>(1, std::min<int64_t>(ts, T / 256));
-  ts = std::max<int64_t>(ts, (T + s.k->max_t_per_wg - 1) / s.k->max_t_per_wg);
-  t_chunk = (T + ts - 1) / ts;
+  const int phases = xeng::row_phases(s.k, (int64_t)s.d.n_chans * s.d.n_inputs);
+  const int64_t rows = (T + phases - 1) / phases;  // of the longest phase
+  int64_t ts = (target + (int64_t)ngroups * phases - 1) / ((int64_t)ngroups * phases);
+  ts = std::max<int64_t>(1, std::min<int64_t>(ts, rows / 256));
+  ts = std::max<int64_t>(ts, (rows + s.k->max_t_per_wg - 1) / s.k->max_t_per_wg);
+  t_chunk = (rows + ts - 1) / ts;
   t_chunk = (t_chunk + xeng::KS - 1) / xeng::KS * xeng::KS;
-  ts = (T + t_chunk - 1) / t_chunk;
+  ts = (rows + t_chunk - 1) / t_chunk * phases;
   grid = dim3((unsigned)ngroups, (unsigned)ts, 1);
   mode = ts > 1 ? xeng::EPI_ATOMIC : (s.clean ? xeng::EPI_STORE : xeng::EPI_ADD);
 }
@@ -157,21 +160,28 @@ bool valid_desc(const xeng_array_desc& d) {
 }
 
 bool kernel_fits(const KernelInfo* k, const xeng_array_desc& d) {
-  return k && (k->max_row_bytes == 0 || (int64_t)d.n_chans * d.n_inputs <= k->max_row_bytes);
+  if (!k) return false;
+  const int64_t row_bytes = (int64_t)d.n_chans * d.n_inputs;
+  return k->max_row_bytes == 0 || row_bytes * xeng::row_phases(k, row_bytes) <= k->max_row_bytes;
 }
 
-// Default kernel for an array: the 16-row-tile ring kernel when N is a
-// multiple of 16 it is built for (and its time rows fit its 32-bit offsets),
-// else the 32-row-tile ring kernel when N is a multiple of 16, else the
-// staging kernel of 16-row tiles.
+// Default kernel for an array: the 16-row-tile ring kernel where it takes N
+// (all but 255) and the time rows fit its 32-bit offsets, else the
+// 32-row-tile ring kernel when N is a multiple of 16, else the staging
+// kernel of 16-row tiles.  Rows taken in phases leave their sums by atomic
+// adds, one per phase, which short phases do not repay (N = 105, F = 93,
+// T = 1532, two calls: 241 us in 16 phases, 88 in the staging kernel; N = 113,
+// F = 933, T = 903: 352 in 4 phases against 308; N = 147, F = 145, T = 2000,
+// 4 phases of 500: 107 against 223; N = 13, F = 999, T = 8192, 16 phases of
+// 512: 62 against 355).
 const KernelInfo* default_kernel(const xeng_array_desc& d) {
   const int32_t n = d.n_inputs;
-  if (n % 16 == 0) {
-    const KernelInfo* k = xeng::x16_kernel(n);
-    if (kernel_fits(k, d)) return k;
-    k = xeng::x32_kernel(n);
-    if (k) return k;
+  const KernelInfo* k = xeng::x16_any_kernel(n, d.n_chans);
+  if (kernel_fits(k, d)) {
+    const int phases = xeng::row_phases(k, (int64_t)d.n_chans * n);
+    if (phases == 1 || d.max_time_per_call / phases >= 256) return k;
   }
+  if (n % 16 == 0 && (k = xeng::x32_kernel(n))) return k;
   return xeng::stage_kernel((n + 15) / 16);
 }
 
@@ -181,7 +191,7 @@ void apply_cached(const xeng_plan_t* p, ArrayState& s, int64_t T) {
   std::lock_guard<std::mutex> lock(g_tune_mu);
   auto it = g_tune.find(key);
   if (it == g_tune.end()) return;
-  const KernelInfo* k = kernel_of(it->second.kind, s.d.n_inputs);
+  const KernelInfo* k = kernel_of(it->second.kind, s.d);
   if (!kernel_fits(k, s.d)) return;
   s.k = k;
   s.split = it->second.split;
@@ -201,7 +211,7 @@ void apply_cached_plan(xeng_plan_t* p, int32_t n_arrays) {
 void record_choice(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
   const TuneKey key{p->arch, p->batched ? 1 : 0, s.d.n_inputs, bucket(s.d.n_chans), bucket(T)};
   std::lock_guard<std::mutex> lock(g_tune_mu);
-  g_tune[key] = TuneVal{kind_of(s.k, s.d.n_inputs), s.split, s.own_launch ? 1 : 0};
+  g_tune[key] = TuneVal{kind_of(s.k, s.d), s.split, s.own_launch ? 1 : 0};
 }
 
 // Untuned time split: two workgroups per CU where the kernel's LDS lets
@@ -264,6 +274,7 @@ xeng::Args base_args(const ArrayState& s, const uint8_t* v, int64_t T) {
   a.T = T;
   a.F = s.d.n_chans;
   a.N = s.d.n_inputs;
+  a.period = xeng::row_phases(s.k, (int64_t)s.d.n_chans * s.d.n_inputs);
   return a;
 }
 
@@ -785,8 +796,8 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
       const ArrayState keep = s;
       ArrayState choice = s;
       for (int kind : {KIND_X16, KIND_X32, KIND_STAGE}) {
-        const KernelInfo* k = kernel_of(kind, s.d.n_inputs);
-        if (!kernel_fits(k, s.d) || (kind != KIND_STAGE && s.d.n_inputs % 16 != 0)) continue;
+        const KernelInfo* k = kernel_of(kind, s.d);
+        if (!kernel_fits(k, s.d) || (kind == KIND_X32 && s.d.n_inputs % 16 != 0)) continue;
         for (int split : {1, 2}) {
           s.k = k;
           s.split = split;
@@ -820,10 +831,8 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
     for (ArrayState& s : p->arrays) {
       if (!s.active) continue;
       std::vector<const KernelInfo*> kernels;
-      if (s.d.n_inputs % 16 == 0) {
-        if (kernel_fits(xeng::x16_kernel(s.d.n_inputs), s.d)) kernels.push_back(xeng::x16_kernel(s.d.n_inputs));
-        kernels.push_back(xeng::x32_kernel(s.d.n_inputs));
-      }
+      if (kernel_fits(kernel_of(KIND_X16, s.d), s.d)) kernels.push_back(kernel_of(KIND_X16, s.d));
+      if (s.d.n_inputs % 16 == 0) kernels.push_back(xeng::x32_kernel(s.d.n_inputs));
       kernels.push_back(xeng::stage_kernel((s.d.n_inputs + 15) / 16));
       const KernelInfo* pick_k = s.k;
       int pick_split = s.split;
