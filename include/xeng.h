@@ -90,7 +90,8 @@ enum {
  *   hip_stream hipStream_t to run on, or NULL for a stream the plan owns.
  * The array indices of later calls are slots 0 .. n_arrays-1 (see
  * xeng_attach for more).  Allocates the HBM-resident int32 accumulators
- * (zeroed).  Errors: EINVAL (null out, null arrays with n_arrays > 0, N or F
+ * (zeroed); a plain plan whose calls are split along time keeps room for the
+ * chunks' sums with them, up to 256 MB.  Errors: EINVAL (null out, null arrays with n_arrays > 0, N or F
  * or max_time_per_call out of range, unknown flags), ENOMEM, EDEVICE.
  */
 int xeng_plan(xeng_plan_t **out, const xeng_array_desc *arrays, int32_t n_arrays,
@@ -218,9 +219,9 @@ int64_t xeng_accumulator_bytes(int32_t n_inputs, int32_t n_chans);
  * (16-row tiles) or as a plain launch of its own inside the same graph, with
  * the tile shape and time split that suit it.  Plain plan, per array: the
  * tile shape (16-row tiles of the 16x16x64 ring kernel, 32-row tiles of the
- * 32x32x32 ring kernel, both for N a multiple of 16, or 16-row tiles of the
+ * 32x32x32 ring kernel for N a multiple of 16, or 16-row tiles of the
  * staging kernel) and the number of workgroups per compute unit that the
- * time split aims for.  The choice is kept by the plan for later calls and
+ * time split aims for (0: the library's model of the call).  The choice is kept by the plan for later calls and
  * entered in the process's tuning cache (xeng_tune_cache_save), which new
  * plans of the same GPU architecture, kind, N and power-of-two buckets of F
  * and of max_time_per_call start from.  Every accumulator must be freshly

@@ -26,7 +26,7 @@ constexpr KernelInfo stage_info() {
   using SH = StageShape<NT>;
   using C = Cfg<NT, SH::W, SH::CPW>;
   return KernelInfo{NT, SH::W, SH::CPW, 2, C::THREADS, C::LDS_BYTES, XENG_MAX_T_PER_WG_STAGE, 0, 16,
-                    &launch_stage<NT>};
+                    &launch_stage<NT>, 0, true, 2};
 }
 
 template <size_t... I>

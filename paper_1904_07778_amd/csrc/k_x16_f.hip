@@ -20,7 +20,7 @@ constexpr KernelInfo info() {
   constexpr int CPW = cpw_for(N), S = stages_for(N, KPS_DEFAULT);
   using C = Shape<N, CPW, S, KPS_DEFAULT>;
   return KernelInfo{C::NT, C::W, CPW, S, C::THREADS, C::LDS_BYTES, MAX_T_PER_WG, MAX_ROW_BYTES, TILE_ROWS,
-                    &launch<N>};
+                    &launch<N>, 0, true, 0};
 }
 
 constexpr int kN[1] = {256};

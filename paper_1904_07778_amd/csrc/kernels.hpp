@@ -17,6 +17,8 @@ struct KernelInfo {
   LaunchFn launch;
   int load_unit = 0;     // ragged kernels: bytes that every row offset must share
                          // (rows are taken in phases where F*N is no multiple); 0: none
+  bool chunks = false;   // honours Args::chunk_stride
+  int split = 1;         // default time split: workgroups per CU to aim for; 0: modelled (choose_split)
 };
 
 // Staging kernel (any N), by 16-row tile count nt = ceil(N/16), 1..16.
@@ -81,7 +83,7 @@ constexpr int ragged_tiles(int n, int unit) { return (n + unit - gcd(n, unit) + 
 // there (N = 200: 299 against 319 us; a chunk load moves 1 KB, a dword load
 // one row of at most 256 bytes).  With a tile more they are slower (N = 230:
 // 461 against 388), and where rows do not start on a chunk they take up to
-// 16 phases against 4 (N = 113, F = 933: 1389 against 352 us).  Below 8
+// 16 phases against 4, each with its own sums to store and add.  Below 8
 // tiles the array is bound by memory and a tile more costs little.  N = 255
 // fits neither (its 258 positions are 17 tiles).
 inline const KernelInfo* x16_any_kernel(int n, int64_t f) {
@@ -124,5 +126,7 @@ struct DumpParams {
   int count;
 };
 hipError_t dump_launch(int grid, hipStream_t s, const DumpParams& d);
+// dst[i] = (prev ? prev[i] : 0) + sum of part[c * n + i] over c < chunks
+hipError_t sum_launch(hipStream_t s, const int2* prev, const int2* part, int2* dst, int64_t n, int chunks);
 
 }  // namespace xeng

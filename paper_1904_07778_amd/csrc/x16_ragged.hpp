@@ -27,7 +27,7 @@ constexpr KernelInfo ragged_info() {
   constexpr int N = 16 * NT, CPW = LD == LD_DWORD ? 1 : cpw_for(N), S = ragged_stages<NT, LD>();
   using C = Shape<N, CPW, S, KPS_DEFAULT, LD>;
   return KernelInfo{C::NT, C::W, CPW, S, C::THREADS, C::LDS_BYTES, MAX_T_PER_WG, MAX_ROW_BYTES, TILE_ROWS,
-                    &ragged_launch<NT, LD>, load_unit(LD)};
+                    &ragged_launch<NT, LD>, load_unit(LD), true, 0};
 }
 
 }  // namespace x16

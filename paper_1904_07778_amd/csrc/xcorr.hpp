@@ -25,7 +25,8 @@
 //   waves: ds_read_b128 of the 16-row fragments, MFMA into register tiles
 //   epilogue: add the tiles into the HBM-resident accumulator: plain stores
 //   right after a dump, read-modify-write when one workgroup owns the
-//   channel, atomics when the time range is split over several workgroups.
+//   channel; when the time range is split over several workgroups, plain
+//   stores of each chunk's sums to be added up, or atomics.
 //
 // Work split inside a channel: see PairPlan below.  Each wave keeps all of its
 // accumulators in registers for the whole time range.
@@ -172,11 +173,13 @@ struct Args {
   int64_t t_chunk;   // samples per workgroup along time (multiple of KS)
   int mode;          // EpiMode
   int period;        // ragged 16-row kernel: phases of time rows (1: one)
+  int64_t chunk_stride;  // time chunk c stores its sums at acc + c * chunk_stride
+                         // (0 but where chunks are summed afterwards)
 };
 
 // How a launch leaves its sums in the accumulator.
 enum EpiMode : int {
-  EPI_STORE = 0,   // accumulator known to be zero: plain stores
+  EPI_STORE = 0,   // accumulator known to be zero, or a chunk's own sums: plain stores
   EPI_ADD = 1,     // one workgroup per channel: read-modify-write
   EPI_ATOMIC = 2   // time range split over workgroups: atomic adds
 };
@@ -194,7 +197,7 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
   constexpr PairPlan<NT, W> plan{};
   constexpr int NS = plan.nseg[WC];
   const int nbl = a.N * (a.N + 1) / 2;
-  int32_t* accf = a.acc + (int64_t)f * nbl * 2;
+  int32_t* accf = a.acc + blockIdx.y * a.chunk_stride + (int64_t)f * nbl * 2;
   const int n = lane & 15;
   const int m0 = 4 * (lane >> 4);
   int idx = 0;

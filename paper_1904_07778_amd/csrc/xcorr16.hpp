@@ -80,7 +80,7 @@ constexpr int MAX_UNITS_PER_WAVE = 60;
 // s must be the same for every row a workgroup sums.  Where the row stride
 // F N is no multiple of the unit, the rows are taken in a.period interleaved
 // phases (row t belongs to phase t % period), one workgroup each, and the
-// phases meet in the accumulator by atomic adds.  The staging kernel, which
+// phases are added up like time chunks.  The staging kernel, which
 // such N used to take, loads single bytes or dwords to registers, transposes
 // and unpacks them there and writes the operands to LDS: at F = 1024, T =
 // 4096, N = 250 took 3091 us there and takes 472 here (N = 200: 882 and 299;
@@ -731,8 +731,10 @@ __device__ __forceinline__ void run_item(const Args& a, uint8_t* lds, int group,
 template <int N, int CPW, int S, int KPS, int LD = LD_EXACT>
 __global__ __launch_bounds__((Shape<N, CPW, S, KPS, LD>::THREADS))
 __attribute__((amdgpu_waves_per_eu(1))) void kernel(Args a) {
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[Shape<N, CPW, S, KPS, LD>::LDS_BYTES];
-  const int wc = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % Shape<N, CPW, S, KPS, LD>::W;
+  using C = Shape<N, CPW, S, KPS, LD>;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[C::LDS_BYTES];
+  const int wc = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % C::W;
+  a.acc += blockIdx.y * a.chunk_stride;
   x16::dispatch<N, CPW, S, KPS, LD, 0>(wc, a, lds, xcd_group(blockIdx.x, gridDim.x), blockIdx.y, threadIdx.x);
 }
 

@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -42,7 +43,9 @@ struct ArrayState {
                        // the next launch overwrites it with plain stores, or
                        // zeroes it first when it must add atomically)
   const KernelInfo* k = nullptr;  // kernel of the plain launch
-  int split = 1;                  // plain launch: aim for split * n_cu workgroups
+  int split = 0;                  // plain launch: aim for split * n_cu workgroups; 0: choose_split
+  int32_t* part = nullptr;        // plain plan: room for part_chunks time chunks' sums, in
+  int part_chunks = 0;            // the accumulator's allocation
   bool own_launch = false;        // batched plan: a plain launch of its own inside the
                                   // graph instead of items of the persistent launch
 };
@@ -134,22 +137,92 @@ bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u
 
 int64_t nbl_of(int32_t n) { return (int64_t)n * (n + 1) / 2; }
 
-// Grid for one call: channel groups x time splits.  Time is split only when
-// the channel groups alone leave the GPU short of workgroups.
-void grid_for(const xeng_plan_t* p, const ArrayState& s, int64_t T, dim3& grid, int64_t& t_chunk,
-              int& mode) {
+constexpr double HBM_BYTES_PER_CYCLE = 13.0;  // 8 TB/s over 256 CUs at 2.4 GHz
+
+double cycles_per_sample(const KernelInfo* k, int32_t n) {
+  // units (real or imaginary product of one tile pair) per channel; a 32-row
+  // unit takes 32 MFMA cycles per 16 samples, a 16-row unit 16 cycles per 32
+  // samples; a workgroup's four SIMDs share its CPW channels' units
+  const int nt = (n + k->tile_rows - 1) / k->tile_rows;
+  const double per_unit = k->tile_rows == 32 ? 2.0 : 0.5;
+  const double mfma = (double)nt * (nt + 1) * per_unit * k->cpw / 4.0;
+  const double hbm = (double)k->cpw * n / HBM_BYTES_PER_CYCLE;
+  return mfma > hbm ? mfma : hbm;
+}
+
+
+// Modelled time of a call of the 16-row ring kernel in ts time chunks per
+// channel group and phase: rounds of workgroups over the CUs, each a start
+// (launch or hand-over, ring fill, epilogue) plus its rows.  A workgroup's
+// rows go at 1.2 times its matrix-core cycles (at 2 GHz), at no more than 25
+// bytes per ns (what one CU streams through its ring, also with most of the
+// chip idle: 24-28 measured for N = 32 .. 112) and at no less than 4 ns a
+// row.  Chunks are stored and summed by a second kernel: its launch, and the
+// store, the read and the sum at 6 bytes per ps (out of the caches mostly);
+// without room for them they are added atomically (115 G adds/s).  Measured
+// against it, kernel times in us for N x F x T: 100x64x4096 in 1, 4, 8, 16
+// chunks 80, 36, 27, 30 (105 with atomics in 16); 192x35x6736 in 1, 4, 8
+// chunks 82, 35, 45; 96x200x4096 in 1, 4, 8 67, 37, 51; 32x64x4096 in 1, 4,
+// 8, 16 25, 16, 12, 13; 128x64x2048 in 1, 2, 4 18, 20, 22.
+double split_us(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int phases, int ts) {
+  const int64_t groups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
+  const int64_t wgs = groups * phases * ts;
+  const double mfma_ns = s.k->nt * (s.k->nt + 1) / (double)s.k->w / 2.0 / 2.0;  // per row: 16 cycles per 32
+  const double row_ns = std::max({1.2 * mfma_ns + 1.0, s.k->cpw * 16.0 * s.k->nt / 25.0, 4.0});
+  const double rounds = (double)((wgs + p->n_cu - 1) / p->n_cu);
+  const double us = rounds * (4.0 + (double)((rows + ts - 1) / ts) * row_ns * 1e-3);
+  const int n = ts * phases;
+  if (n == 1) return us;
+  const double acc = (double)s.acc_bytes;
+  return us + 5.0 + (n <= s.part_chunks ? (2 * n + 1) * acc / 6e6 : n * acc / 4.0 / 115e3);
+}
+
+// Time split of an untuned array: the workgroups per channel group (and
+// phase) with the least modelled time.
+int choose_split(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int phases) {
+  double best = 0;
+  int pick = 1;
+  for (int ts = 1; ts <= 64 && (ts == 1 || rows / ts >= 64); ++ts) {
+    const double us = split_us(p, s, rows, phases, ts);
+    if (best == 0 || us < best) best = us, pick = ts;
+  }
+  return pick;
+}
+
+// One call's launch, and how its sums reach the accumulator.
+struct Grid {
+  dim3 dim;         // channel groups x time chunks
+  int64_t t_chunk;  // rows of a chunk
+  int mode;         // EpiMode
+  bool parts;       // the chunks are stored in s.part and summed by a second kernel
+  int chunks;       // of them, those that hold samples
+};
+
+Grid grid_for(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
   const int ngroups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
-  const int64_t target = (int64_t)s.split * p->n_cu;
   const int phases = xeng::row_phases(s.k, (int64_t)s.d.n_chans * s.d.n_inputs);
   const int64_t rows = (T + phases - 1) / phases;  // of the longest phase
-  int64_t ts = (target + (int64_t)ngroups * phases - 1) / ((int64_t)ngroups * phases);
-  ts = std::max<int64_t>(1, std::min<int64_t>(ts, rows / 256));
+  int64_t ts;
+  if (s.split > 0) {
+    const int64_t target = (int64_t)s.split * p->n_cu;
+    ts = (target + (int64_t)ngroups * phases - 1) / ((int64_t)ngroups * phases);
+    ts = std::max<int64_t>(1, std::min<int64_t>(ts, rows / 256));
+  } else {
+    ts = choose_split(p, s, rows, phases);
+  }
   ts = std::max<int64_t>(ts, (rows + s.k->max_t_per_wg - 1) / s.k->max_t_per_wg);
-  t_chunk = (rows + ts - 1) / ts;
-  t_chunk = (t_chunk + xeng::KS - 1) / xeng::KS * xeng::KS;
-  ts = (rows + t_chunk - 1) / t_chunk * phases;
-  grid = dim3((unsigned)ngroups, (unsigned)ts, 1);
-  mode = ts > 1 ? xeng::EPI_ATOMIC : (s.clean ? xeng::EPI_STORE : xeng::EPI_ADD);
+  Grid g{};
+  g.t_chunk = (rows + ts - 1) / ts;
+  g.t_chunk = (g.t_chunk + xeng::KS - 1) / xeng::KS * xeng::KS;
+  ts = (rows + g.t_chunk - 1) / g.t_chunk * phases;
+  g.dim = dim3((unsigned)ngroups, (unsigned)ts, 1);
+  g.parts = s.k->chunks && ts > 1 && ts <= s.part_chunks;
+  // the last chunk of a phase may be empty: phase ph has rows left while
+  // last * t_chunk * phases + ph < T
+  const int64_t before = ts - phases;
+  g.chunks = (int)(before + std::min<int64_t>(phases, T - before / phases * g.t_chunk * phases));
+  g.mode = ts > 1 ? (g.parts ? xeng::EPI_STORE : xeng::EPI_ATOMIC) : (s.clean ? xeng::EPI_STORE : xeng::EPI_ADD);
+  return g;
 }
 
 
@@ -168,18 +241,21 @@ bool kernel_fits(const KernelInfo* k, const xeng_array_desc& d) {
 // Default kernel for an array: the 16-row-tile ring kernel where it takes N
 // (all but 255) and the time rows fit its 32-bit offsets, else the
 // 32-row-tile ring kernel when N is a multiple of 16, else the staging
-// kernel of 16-row tiles.  Rows taken in phases leave their sums by atomic
-// adds, one per phase, which short phases do not repay (N = 105, F = 93,
-// T = 1532, two calls: 241 us in 16 phases, 88 in the staging kernel; N = 113,
-// F = 933, T = 903: 352 in 4 phases against 308; N = 147, F = 145, T = 2000,
-// 4 phases of 500: 107 against 223; N = 13, F = 999, T = 8192, 16 phases of
-// 512: 62 against 355).
+// kernel of 16-row tiles.  Rows taken in phases make a workgroup and a chunk
+// of sums per phase, which many channels and few rows do not repay (kernel
+// times: N = 61, F = 513, T = 1000, 2064 workgroups of 62 rows 80 us against
+// 68 in the staging kernel; N = 7, F = 1001, T = 300 30 against 28; but N =
+// 51, F = 77, T = 500, 320 workgroups of 31 rows 24 against 49, and N = 113,
+// F = 933, T = 903, 3732 of 226 rows 129 against 236).
+constexpr int64_t MIN_PHASE_ROWS = 64, MANY_WORKGROUPS = 1024;
+
 const KernelInfo* default_kernel(const xeng_array_desc& d) {
   const int32_t n = d.n_inputs;
   const KernelInfo* k = xeng::x16_any_kernel(n, d.n_chans);
   if (kernel_fits(k, d)) {
     const int phases = xeng::row_phases(k, (int64_t)d.n_chans * n);
-    if (phases == 1 || d.max_time_per_call / phases >= 256) return k;
+    const int64_t wgs = (int64_t)((d.n_chans + k->cpw - 1) / k->cpw) * phases;
+    if (phases == 1 || d.max_time_per_call / phases >= MIN_PHASE_ROWS || wgs <= MANY_WORKGROUPS) return k;
   }
   if (n % 16 == 0 && (k = xeng::x32_kernel(n))) return k;
   return xeng::stage_kernel((n + 15) / 16);
@@ -214,26 +290,30 @@ void record_choice(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
   g_tune[key] = TuneVal{kind_of(s.k, s.d), s.split, s.own_launch ? 1 : 0};
 }
 
-// Untuned time split: two workgroups per CU where the kernel's LDS lets
-// several share a CU (the staging kernel, the ring kernel at N = 16), one
-// where its ring fills most of the CU's LDS: a second workgroup could not
-// run beside the first, and aiming for it only splits time into atomic adds
-// and a zeroing pass (45-60% slower at N = 48..112, F = 1024).
-int default_split(const KernelInfo* k) { return k->lds_bytes <= 64 * 1024 ? 2 : 1; }
+constexpr size_t MAX_PART_BYTES = (size_t)256 << 20;
 
 int init_slot(xeng_plan_t* p, ArrayState& s, const xeng_array_desc& d) {
   s = ArrayState{};
   s.d = d;
   s.k = default_kernel(d);
-  s.split = default_split(s.k);
+  s.split = s.k->split;
   apply_cached(p, s, d.max_time_per_call);
   s.acc_bytes = (size_t)d.n_chans * nbl_of(d.n_inputs) * 2 * sizeof(int32_t);
-  hipError_t e = hipMalloc(&s.acc, s.acc_bytes);
+  // A plain plan keeps room for the sums of the time chunks of its longest
+  // call (bounded; calls split further add atomically).
+  if (!p->batched && s.k->chunks) {
+    s.part_chunks = INT_MAX;
+    const Grid g = grid_for(p, s, d.max_time_per_call);
+    s.part_chunks = g.parts && g.dim.y * s.acc_bytes <= MAX_PART_BYTES ? (int)g.dim.y : 0;
+  }
+  const size_t acc_room = s.part_chunks ? (s.acc_bytes + 255) / 256 * 256 : s.acc_bytes;
+  hipError_t e = hipMalloc(&s.acc, acc_room + s.part_chunks * s.acc_bytes);
   if (e != hipSuccess) {
     s.acc = nullptr;
     return e == hipErrorOutOfMemory ? fail(p, XENG_ENOMEM, "accumulator of %zu bytes", s.acc_bytes)
                                     : hip_fail(p, e, "accumulator allocation");
   }
+  if (s.part_chunks) s.part = s.acc + acc_room / sizeof(int32_t);
   e = hipMemsetAsync(s.acc, 0, s.acc_bytes, p->stream);
   if (e != hipSuccess) return hip_fail(p, e, "accumulator clear");
   s.active = true;
@@ -280,17 +360,26 @@ xeng::Args base_args(const ArrayState& s, const uint8_t* v, int64_t T) {
 
 int launch_plain(xeng_plan_t* p, ArrayState& s, const uint8_t* v, int64_t T) {
   xeng::Args args = base_args(s, v, T);
-  dim3 grid;
-  grid_for(p, s, T, grid, args.t_chunk, args.mode);
+  const Grid g = grid_for(p, s, T);
+  args.t_chunk = g.t_chunk;
+  args.mode = g.mode;
+  if (g.parts) {
+    args.acc = s.part;
+    args.chunk_stride = (int64_t)(s.acc_bytes / sizeof(int32_t));
+  }
   ++p->stats.launches;
   if (p->trace)
-    fprintf(stderr, "xeng: plan %p plain launch N=%d F=%d T=%lld grid=%ux%u threads=%d mode=%d\n", (void*)p,
-            args.N, args.F, (long long)T, grid.x, grid.y, s.k->threads, args.mode);
+    fprintf(stderr, "xeng: plan %p plain launch N=%d F=%d T=%lld grid=%ux%u threads=%d mode=%d chunks=%d\n", (void*)p,
+            args.N, args.F, (long long)T, g.dim.x, g.dim.y, s.k->threads, args.mode, g.parts ? g.chunks : 0);
   if (args.mode == xeng::EPI_ATOMIC && s.clean && !s.zeroed) {
     const int st = zero_fill(p, {&s});
     if (st != XENG_OK) return st;
   }
-  hipError_t e = s.k->launch(grid, p->stream, args);
+  hipError_t e = s.k->launch(g.dim, p->stream, args);
+  if (e == hipSuccess && g.parts)
+    e = xeng::sum_launch(p->stream, s.clean ? nullptr : reinterpret_cast<const int2*>(s.acc),
+                         reinterpret_cast<const int2*>(s.part), reinterpret_cast<int2*>(s.acc),
+                         (int64_t)(s.acc_bytes / sizeof(int2)), g.chunks);
   return e == hipSuccess ? XENG_OK : hip_fail(p, e, "kernel launch");
 }
 
@@ -302,19 +391,6 @@ int launch_plain(xeng_plan_t* p, ArrayState& s, const uint8_t* v, int64_t T) {
 // per sample, plus a fixed start-up cost per item); arrays are queued longest
 // item first.
 constexpr double ITEM_START_CYCLES = 4000.0;  // ring fill and epilogue of one item
-constexpr double HBM_BYTES_PER_CYCLE = 13.0;  // 8 TB/s over 256 CUs at 2.4 GHz
-
-double cycles_per_sample(const KernelInfo* k, int32_t n) {
-  // units (real or imaginary product of one tile pair) per channel; a 32-row
-  // unit takes 32 MFMA cycles per 16 samples, a 16-row unit 16 cycles per 32
-  // samples; a workgroup's four SIMDs share its CPW channels' units
-  const int nt = (n + k->tile_rows - 1) / k->tile_rows;
-  const double per_unit = k->tile_rows == 32 ? 2.0 : 0.5;
-  const double mfma = (double)nt * (nt + 1) * per_unit * k->cpw / 4.0;
-  const double hbm = (double)k->cpw * n / HBM_BYTES_PER_CYCLE;
-  return mfma > hbm ? mfma : hbm;
-}
-
 struct BatchEntry {
   int32_t a;
   int32_t ngroups, nchunks;
@@ -839,7 +915,8 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
       float arr_best = 0;
       for (const KernelInfo* k : kernels) {
         if (!k) continue;
-        for (int split : {1, 2, 4}) {
+        for (int split : {0, 1, 2, 4}) {
+          if (split == 0 && k->split != 0) continue;  // no model for this kernel
           s.k = k;
           s.split = split;
           float ms = 0;
@@ -895,8 +972,8 @@ int xeng_tune_cache_load(const char* path) {
     char arch[128];
     int b, n, fb, tb, kind, split, own;
     if (sscanf(line, "%127s %d %d %d %d %d %d %d", arch, &b, &n, &fb, &tb, &kind, &split, &own) != 8 ||
-        n < 0 || n > XENG_MAX_INPUTS || (n == 0 && !b) || kind < KIND_X16 || kind > KIND_STAGE || split < 1 ||
-        split > 64) {
+        n < 0 || n > XENG_MAX_INPUTS || (n == 0 && !b) || kind < KIND_X16 || kind > KIND_STAGE ||
+        split < (b || kind != KIND_X16 ? 1 : 0) || split > 64) {
       st = XENG_EINVAL;  // malformed line: skipped, reported
       continue;
     }

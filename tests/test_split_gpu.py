@@ -1,0 +1,60 @@
+"""Calls split along time: each workgroup stores its chunk's sums and a second
+kernel adds them up, with earlier samples of the integration.  Ring kernel
+(whole and ragged N, one and several phases) and staging kernel (N = 255),
+few channels so that every call is split; short and long calls of one
+integration and snapshots.  Integer work: equal to the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import first_mismatch, gpu_available
+
+pytestmark = pytest.mark.gpu
+if not gpu_available():
+    pytestmark = [pytest.mark.gpu, pytest.mark.skip(reason="no GPU")]
+
+
+@pytest.mark.parametrize("N,F", [(16, 1), (32, 4), (48, 3), (100, 4), (101, 3), (176, 2), (200, 2), (250, 1), (255, 1)])
+def test_split_calls_of_one_integration(N, F):
+    import torch
+    from paper_1904_07778_amd.xeng import Plan
+    print(f"split N={N} F={F}", flush=True)
+    rng = np.random.default_rng(N)
+    blocks = [rng.integers(0, 256, size=(t, F, N), dtype=np.uint8) for t in (4000, 129, 4000, 2050)]
+    dev = [torch.from_numpy(b).cuda() for b in blocks]
+    with Plan([(N, F, 4000)]) as p:
+        for _ in range(2):
+            e = oracle.Engine(N, F)
+            for b, d in zip(blocks[:-1], dev):
+                e.correlate(b)
+                p.correlate([d])
+                snap, _ = p.dump(keep=True, to_host=True)
+                want = e.dump(keep=True)[0]
+                assert np.array_equal(snap[0].numpy(), want), first_mismatch(snap[0].numpy(), want)
+            e.correlate(blocks[-1])
+            out, n = p.correlate_dump([dev[-1]])
+            torch.cuda.synchronize()
+            want = e.dump()[0]
+            got = out[0].cpu().numpy()
+            assert n == [10179] and np.array_equal(got, want), first_mismatch(got, want)
+
+
+def test_one_long_call():
+    """One channel over 400,000 samples: the longest chunk a workgroup may
+    integrate (32768) sets the split, after a short call on the same plan."""
+    import torch
+    from paper_1904_07778_amd.xeng import Plan
+    N, F, T = 240, 1, 400000
+    rng = np.random.default_rng(5)
+    v = rng.integers(0, 256, size=(T, F, N), dtype=np.uint8)
+    d = torch.from_numpy(v).cuda()
+    e = oracle.Engine(N, F)
+    e.correlate(v)
+    want = e.dump()[0]
+    with Plan([(N, F, T)]) as p:
+        for _ in range(2):
+            p.correlate([d[:100]])
+            _, _ = p.dump(to_host=True)
+            p.correlate([d])
+            out, _ = p.dump(to_host=True)
+            assert np.array_equal(out[0].numpy(), want), first_mismatch(out[0].numpy(), want)
