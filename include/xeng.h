@@ -329,25 +329,18 @@ int xeng_ingest(const uint8_t *d_packets, int64_t n_packets, int32_t packet_stri
  *               xeng_channelise_spectra; channel k < F (Nyquist dropped).
  *               May be NULL when there are no spectra.
  *   d_tables    float [xeng_channelise_table_floats(F)], device, 16-byte
- *               aligned: scratch for the filter and twiddle tables, written
- *               by the call (caller-owned; one per concurrent call).
+ *               aligned: scratch, checked but no longer used (the filter and
+ *               twiddle tables are part of the library).
  * Errors: EINVAL (sizes, alignment, null pointers), EDEVICE.
  */
 int xeng_channelise(const int8_t *d_adc, int64_t n_samples, int32_t n_inputs, int32_t n_chans,
                     float *d_out, float *d_tables, void *hip_stream);
 
 /*
- * xeng_channelise_noalloc - xeng_channelise for callers that cannot allocate
- * device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid allocation): the same computation and arguments without
- * d_tables.  The filter and twiddle tables go to a scratch array inside the
- * library, one per GPU, of 4 * 2048 + 2048 floats (40 KB, enough for the
- * largest spectrum, F = 1024), held until the process ends; the call itself
- * allocates nothing.  Every call on a GPU rewrites that GPU's array before
- * reading it, so calls that overlap on one GPU (on different streams) race
- * and must not be issued.  Errors: as xeng_channelise (EINVAL also for F
- * beyond the scratch size), EDEVICE if the scratch address cannot be
- * obtained.
+ * xeng_channelise_noalloc - xeng_channelise without d_tables: the same
+ * computation and arguments otherwise, for callers that cannot allocate
+ * device memory (code under HIP graph capture, tight serving loops).
+ * Errors: as xeng_channelise.
  */
 int xeng_channelise_noalloc(const int8_t *d_adc, int64_t n_samples, int32_t n_inputs, int32_t n_chans,
                             float *d_out, void *hip_stream);

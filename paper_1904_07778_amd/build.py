@@ -36,6 +36,8 @@ HIPCC_FLAGS = [
 PER_FILE_FLAGS = {
     "k_x16_": ["-mllvm", "-greedy-reverse-local-assignment"],
     "k_batch": ["-mllvm", "-greedy-reverse-local-assignment"],
+    # the channeliser's tables are evaluated at compile time
+    "k_chan": ["-fconstexpr-steps=100000000"],
 }
 # the host pass warns that it does not know the packed-fp32 feature
 _NOISE = ("'-packed-fp32-ops' is not a recognized feature",)
