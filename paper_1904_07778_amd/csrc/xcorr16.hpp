@@ -310,9 +310,9 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
         sfor<0, 4>([&](auto v) {
           site(u, v, [&](auto pair, auto im, int32_t* dst, int, int) {
             if constexpr (pair.value)
-              prev[u - u0][v] = *reinterpret_cast<const v2i*>(dst);
+              prev[u - u0][v] = *reinterpret_cast<const v2i*>(dst + a.prev_off);
             else
-              prev[u - u0][v][0] = dst[im.value];
+              prev[u - u0][v][0] = dst[a.prev_off + im.value];
           });
         });
       });

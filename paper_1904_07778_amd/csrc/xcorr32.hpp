@@ -234,9 +234,9 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
       v2i prev[CH][16];
       sites(U0{}, U1{}, [&](auto u, auto v, auto pair, auto im, int32_t* dst, int) {
         if constexpr (pair.value)
-          prev[u - u0][v] = *reinterpret_cast<const v2i*>(dst);
+          prev[u - u0][v] = *reinterpret_cast<const v2i*>(dst + a.prev_off);
         else
-          prev[u - u0][v][0] = dst[im.value];
+          prev[u - u0][v][0] = dst[a.prev_off + im.value];
       });
       sites(U0{}, U1{}, [&](auto u, auto v, auto pair, auto im, int32_t* dst, int32_t bias) {
         const v2i r = value(u, v, pair, bias);

@@ -42,6 +42,8 @@ struct ArrayState {
   bool zeroed = true;  // accumulator memory holds zeros (a dump does not clear it:
                        // the next launch overwrites it with plain stores, or
                        // zeroes it first when it must add atomically)
+  const int32_t* prev = nullptr;  // during xeng_correlate_dump: the earlier samples' sums,
+                                  // while acc is the caller's destination
   const KernelInfo* k = nullptr;  // kernel of the plain launch
   int split = 0;                  // plain launch: aim for split * n_cu workgroups; 0: choose_split
   int32_t* part = nullptr;        // plain plan: room for part_chunks time chunks' sums, in
@@ -320,9 +322,10 @@ int init_slot(xeng_plan_t* p, ArrayState& s, const xeng_array_desc& d) {
   return XENG_OK;
 }
 
-// Zero the accumulators of the given arrays with one kernel launch (the dump
-// kernel with a null source), so the launch may be recorded into a graph.
-int zero_fill(xeng_plan_t* p, const std::vector<ArrayState*>& arrays) {
+// Give the accumulators of the given arrays the values that atomic adds start
+// from, with one launch of the dump kernel (which may be recorded into a
+// graph): the earlier samples' sums, or zeros.
+int init_for_atomics(xeng_plan_t* p, const std::vector<ArrayState*>& arrays) {
   xeng::DumpParams dp{};
   int64_t most = 0;
   auto flush = [&]() -> int {
@@ -334,11 +337,11 @@ int zero_fill(xeng_plan_t* p, const std::vector<ArrayState*>& arrays) {
     return e == hipSuccess ? XENG_OK : hip_fail(p, e, "accumulator clear");
   };
   for (ArrayState* s : arrays) {
-    dp.acc[dp.count] = nullptr;
+    dp.acc[dp.count] = reinterpret_cast<const int2*>(s->prev);
     dp.dst[dp.count] = reinterpret_cast<int2*>(s->acc);
     dp.n[dp.count] = (int64_t)(s->acc_bytes / sizeof(int2));
     most = std::max(most, dp.n[dp.count]);
-    s->zeroed = true;
+    s->zeroed = s->clean;
     if (++dp.count == xeng::DUMP_MAX) {
       const int st = flush();
       if (st != XENG_OK) return st;
@@ -346,6 +349,10 @@ int zero_fill(xeng_plan_t* p, const std::vector<ArrayState*>& arrays) {
   }
   return flush();
 }
+
+// Whether a launch that adds atomically needs that first: an empty
+// integration in memory that does not hold zeros, or earlier sums elsewhere.
+bool needs_init(const ArrayState& s) { return s.clean ? !s.zeroed : s.prev != nullptr; }
 
 xeng::Args base_args(const ArrayState& s, const uint8_t* v, int64_t T) {
   xeng::Args a{};
@@ -355,6 +362,9 @@ xeng::Args base_args(const ArrayState& s, const uint8_t* v, int64_t T) {
   a.F = s.d.n_chans;
   a.N = s.d.n_inputs;
   a.period = xeng::row_phases(s.k, (int64_t)s.d.n_chans * s.d.n_inputs);
+  if (s.prev)
+    a.prev_off = (int64_t)(reinterpret_cast<uintptr_t>(s.prev) - reinterpret_cast<uintptr_t>(s.acc)) /
+                 (int64_t)sizeof(int32_t);
   return a;
 }
 
@@ -371,13 +381,13 @@ int launch_plain(xeng_plan_t* p, ArrayState& s, const uint8_t* v, int64_t T) {
   if (p->trace)
     fprintf(stderr, "xeng: plan %p plain launch N=%d F=%d T=%lld grid=%ux%u threads=%d mode=%d chunks=%d\n", (void*)p,
             args.N, args.F, (long long)T, g.dim.x, g.dim.y, s.k->threads, args.mode, g.parts ? g.chunks : 0);
-  if (args.mode == xeng::EPI_ATOMIC && s.clean && !s.zeroed) {
-    const int st = zero_fill(p, {&s});
+  if (args.mode == xeng::EPI_ATOMIC && needs_init(s)) {
+    const int st = init_for_atomics(p, {&s});
     if (st != XENG_OK) return st;
   }
   hipError_t e = s.k->launch(g.dim, p->stream, args);
   if (e == hipSuccess && g.parts)
-    e = xeng::sum_launch(p->stream, s.clean ? nullptr : reinterpret_cast<const int2*>(s.acc),
+    e = xeng::sum_launch(p->stream, s.clean ? nullptr : reinterpret_cast<const int2*>(s.prev ? s.prev : s.acc),
                          reinterpret_cast<const int2*>(s.part), reinterpret_cast<int2*>(s.acc),
                          (int64_t)(s.acc_bytes / sizeof(int2)), g.chunks);
   return e == hipSuccess ? XENG_OK : hip_fail(p, e, "kernel launch");
@@ -431,14 +441,13 @@ int record_batched(xeng_plan_t* p, const uint8_t* const* v, const int64_t* n_tim
   }
   std::stable_sort(items.begin(), items.end(),
                    [](const BatchEntry& x, const BatchEntry& y) { return x.item_cycles > y.item_cycles; });
-  // arrays that start an integration with atomic adds need zeroed memory
-  std::vector<ArrayState*> to_zero;
+  std::vector<ArrayState*> to_init;
   for (const BatchEntry& b : items) {
     ArrayState& s = p->arrays[b.a];
-    if (b.nchunks > 1 && s.clean && !s.zeroed) to_zero.push_back(&s);
+    if (b.nchunks > 1 && needs_init(s)) to_init.push_back(&s);
   }
-  if (!to_zero.empty()) {
-    const int st = zero_fill(p, to_zero);
+  if (!to_init.empty()) {
+    const int st = init_for_atomics(p, to_init);
     if (st != XENG_OK) return st;
   }
   for (size_t first = 0; first < items.size(); first += xeng::batch::MAX_ARRAYS) {
@@ -746,9 +755,8 @@ int xeng_correlate_dump(xeng_plan_t* p, const uint8_t* const* d_voltages, const 
     st = xeng_dump(p, a, dst, 0, n_integrated ? n_integrated + a : nullptr);
     if (st != XENG_OK) return st;
   }
-  // The others integrate straight into their destination: an empty
-  // integration starts there from nothing (plain stores, or atomic adds into
-  // zeroed memory); earlier samples are copied over first and added to.
+  // The others integrate straight into their destination, from nothing or
+  // from the accumulator's earlier samples.
   struct Saved {
     int32_t a;
     int32_t* acc;
@@ -756,42 +764,19 @@ int xeng_correlate_dump(xeng_plan_t* p, const uint8_t* const* d_voltages, const 
     int64_t n;
   };
   std::vector<Saved> redirected;
-  xeng::DumpParams dp{};
-  int64_t most = 0;
-  auto flush = [&]() -> int {
-    if (dp.count == 0) return XENG_OK;
-    const int64_t blocks = std::min<int64_t>((most + 1023) / 1024, 8LL * p->n_cu);
-    hipError_t e = xeng::dump_launch((int)std::max<int64_t>(1, blocks), p->stream, dp);
-    dp.count = 0;
-    most = 0;
-    return e == hipSuccess ? XENG_OK : hip_fail(p, e, "carry-over copy");
-  };
   for (int32_t a = 0; a < na; ++a) {
     ArrayState& s = p->arrays[a];
     if (!s.active || !d_dst[a] || n_time[a] == 0) continue;
     redirected.push_back(Saved{a, s.acc, s.clean, s.zeroed, s.n_integrated});
-    if (!s.clean) {
-      dp.acc[dp.count] = reinterpret_cast<const int2*>(s.acc);
-      dp.dst[dp.count] = reinterpret_cast<int2*>(d_dst[a]);
-      dp.n[dp.count] = (int64_t)(s.acc_bytes / sizeof(int2));
-      most = std::max(most, dp.n[dp.count]);
-      if (++dp.count == xeng::DUMP_MAX) {
-        st = flush();
-        if (st != XENG_OK) return st;
-      }
-    }
-  }
-  st = flush();
-  if (st != XENG_OK) return st;
-  for (const Saved& r : redirected) {
-    ArrayState& s = p->arrays[r.a];
-    s.acc = d_dst[r.a];
+    s.prev = s.clean ? nullptr : s.acc;
+    s.acc = d_dst[a];
     s.zeroed = false;  // clean (empty) destinations hold unknown values
   }
   st = correlate_unchecked(p, d_voltages, n_time);
   for (const Saved& r : redirected) {
     ArrayState& s = p->arrays[r.a];
     s.acc = r.acc;
+    s.prev = nullptr;
     if (st != XENG_OK) {
       s.clean = r.clean;
       s.zeroed = r.zeroed;
@@ -1033,7 +1018,7 @@ int xeng_dump(xeng_plan_t* p, int32_t array, int32_t* const* dst, uint32_t flags
       }
     } else {
       if (stale) {
-        const int st = zero_fill(p, {&s});
+        const int st = init_for_atomics(p, {&s});
         if (st != XENG_OK) return st;
       }
       hipError_t e = hipMemcpyAsync(d, s.acc, s.acc_bytes,

@@ -58,3 +58,30 @@ def test_one_long_call():
             p.correlate([d])
             out, _ = p.dump(to_host=True)
             assert np.array_equal(out[0].numpy(), want), first_mismatch(out[0].numpy(), want)
+
+
+@pytest.mark.parametrize("T", [200, 3000])
+def test_last_block_of_an_integration_in_a_batch(T):
+    """correlate, then correlate_dump into fresh buffers: the earlier sums are
+    read from the accumulator (one chunk per item), or copied over first
+    (items split along time), for arrays inside the persistent launch and on
+    launches of their own; the next integration starts empty."""
+    import torch
+    from paper_1904_07778_amd.xeng import Plan
+    shapes = [(192, 3, T), (32, 5, T), (40, 16, T), (255, 1, T)]
+    rng = np.random.default_rng(T)
+    vs = [rng.integers(0, 256, size=(t, f, n), dtype=np.uint8) for n, f, t in shapes]
+    dev = [torch.from_numpy(v).cuda() for v in vs]
+    print(f"last block T={T}", flush=True)
+    with Plan(shapes) as p:
+        for _ in range(2):
+            p.correlate(dev)
+            p.correlate([dev[0], None, dev[2], None])
+            out = [torch.full_like(p.new_output(a), -1) for a in range(len(shapes))]
+            _, n = p.correlate_dump(dev, out=out)
+            torch.cuda.synchronize()
+            assert n == [3 * T, 2 * T, 3 * T, 2 * T]
+            for v, o, k in zip(vs, out, n):
+                want = oracle.to_int32(oracle.accumulate(v) * (k // T))
+                got = o.cpu().numpy()
+                assert np.array_equal(got, want), first_mismatch(got, want)
