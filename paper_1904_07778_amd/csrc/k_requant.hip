@@ -17,7 +17,7 @@
 // floor(P / 2^21) = (A >> 12) + (R >> 21) and P mod 2^21 = R & (2^21 - 1).
 //
 // Memory: the kernel streams T*F*N*8 bytes in and T*F*N bytes out, once
-// (HBM-bound).  Each thread walks down ROWS time rows (rows are F*N samples
+// (HBM-bound).  Each thread walks down up to 16 time rows (rows are F*N samples
 // apart), keeping its gains in registers.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -31,7 +31,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int THREADS = 256;
-constexpr int ROWS = 16;  // time rows per thread
+constexpr int MAX_ROWS = 16;  // time rows per thread at most
 
 __device__ __forceinline__ int sext18(uint32_t x) { return ((int)(x << 14)) >> 14; }
 
@@ -53,16 +53,16 @@ __device__ __forceinline__ uint32_t byte_of(uint64_t w, int g) {
 
 // Fast path: F*N even, words 16-byte, gains 8-byte, output 2-byte aligned.
 // A wave owns 512 consecutive samples of a row (256 pairs) and walks down
-// ROWS rows with the 8 gains of each lane in registers.  Per instruction the
+// its rows with the 8 gains of each lane in registers.  Per instruction the
 // 64 lanes load 64 consecutive 16-byte pairs (1 KB) and store 64 consecutive
 // 2-byte pairs (128 bytes): fully coalesced.
 __global__ __launch_bounds__(THREADS) void requant8(const uint64_t* __restrict__ w,
                                                     const uint32_t* __restrict__ gains,
-                                                    uint8_t* __restrict__ out, int64_t T, int64_t fn2) {
+                                                    uint8_t* __restrict__ out, int64_t T, int64_t fn2, int rows) {
   const int lane = threadIdx.x & 63;
   const int64_t chunk = (int64_t)blockIdx.x * (THREADS / 64) + (threadIdx.x >> 6);  // 256 pairs each
-  const int64_t t0 = (int64_t)blockIdx.y * ROWS;
-  const int64_t t1 = min(T, t0 + ROWS);
+  const int64_t t0 = (int64_t)blockIdx.y * rows;
+  const int64_t t1 = min(T, t0 + rows);
   int64_t pr[4];
   bool ok[4];
   int g[8];
@@ -96,11 +96,11 @@ __global__ __launch_bounds__(THREADS) void requant8(const uint64_t* __restrict__
 // General path: any F*N and alignment (8-byte words, 4-byte gains).
 __global__ __launch_bounds__(THREADS) void requant1(const uint64_t* __restrict__ w,
                                                     const uint32_t* __restrict__ gains,
-                                                    uint8_t* __restrict__ out, int64_t T, int64_t fn) {
+                                                    uint8_t* __restrict__ out, int64_t T, int64_t fn, int rows) {
   const int64_t x = (int64_t)blockIdx.x * THREADS + threadIdx.x;
   if (x >= fn) return;
-  const int64_t t0 = (int64_t)blockIdx.y * ROWS;
-  const int64_t t1 = min(T, t0 + ROWS);
+  const int64_t t0 = (int64_t)blockIdx.y * rows;
+  const int64_t t1 = min(T, t0 + rows);
   const int g = gains[x] & 0x3FFFF;
   for (int64_t t = t0; t < t1; ++t) out[t * fn + x] = (uint8_t)byte_of(w[t * fn + x], g);
 }
@@ -166,8 +166,6 @@ extern "C" int xeng_requantize(const uint64_t* d_words, const uint32_t* d_gains,
     return XENG_EINVAL;
   if (n_time == 0) return XENG_OK;
   const int64_t fn = (int64_t)n_chans * n_inputs;
-  const int64_t ty = (n_time + xeng::ROWS - 1) / xeng::ROWS;
-  if (ty > 2147483647LL) return XENG_EINVAL;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   const bool fast = fn % 2 == 0 && (reinterpret_cast<uintptr_t>(d_words) & 15u) == 0 &&
                     (reinterpret_cast<uintptr_t>(d_out) & 1u) == 0 &&
@@ -175,11 +173,19 @@ extern "C" int xeng_requantize(const uint64_t* d_words, const uint32_t* d_gains,
   const int64_t cols = fast ? fn / 2 : fn;                      // pairs, or samples
   const int64_t per_wg = fast ? 256 * (xeng::THREADS / 64) : xeng::THREADS;
   const int64_t gx = (cols + per_wg - 1) / per_wg;
-  if (gx > 2147483647LL) return XENG_EINVAL;
+  if (gx > 2147483647LL || (n_time + xeng::MAX_ROWS - 1) / xeng::MAX_ROWS > 2147483647LL) return XENG_EINVAL;
+  // Rows per thread: as many as keep the gains in registers longest while the
+  // grid still fills every wave slot (8 workgroups on each of 256 CUs): a
+  // thread's rows go one after the other, each a memory round trip.  (N = 32,
+  // F = 512, T = 512: 32 us in 256 workgroups of 16 rows, 17 in 2048 of 2; N = 158, F = 77,
+  // T = 134: 30 and 6.)
+  const int64_t room = n_time * gx / (8 * 256);
+  const int rows = (int)(room < 1 ? 1 : room > xeng::MAX_ROWS ? xeng::MAX_ROWS : room);
+  const int64_t ty = (n_time + rows - 1) / rows;
   const dim3 grid((unsigned)gx, (unsigned)ty);
   if (fast)
-    hipLaunchKernelGGL(xeng::requant8, grid, dim3(xeng::THREADS), 0, s, d_words, d_gains, d_out, n_time, cols);
+    hipLaunchKernelGGL(xeng::requant8, grid, dim3(xeng::THREADS), 0, s, d_words, d_gains, d_out, n_time, cols, rows);
   else
-    hipLaunchKernelGGL(xeng::requant1, grid, dim3(xeng::THREADS), 0, s, d_words, d_gains, d_out, n_time, cols);
+    hipLaunchKernelGGL(xeng::requant1, grid, dim3(xeng::THREADS), 0, s, d_words, d_gains, d_out, n_time, cols, rows);
   return hipGetLastError() == hipSuccess ? XENG_OK : XENG_EDEVICE;
 }
