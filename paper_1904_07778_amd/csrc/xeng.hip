@@ -48,6 +48,9 @@ struct ArrayState {
   int split = 0;                  // plain launch: aim for split * n_cu workgroups; 0: choose_split
   int32_t* part = nullptr;        // plain plan: room for part_chunks time chunks' sums, in
   int part_chunks = 0;            // the accumulator's allocation
+  mutable const KernelInfo* split_kernel = nullptr;  // choose_split's last pick: it depends on
+  mutable int64_t split_rows = -1;                   // the kernel and a call's rows alone
+  mutable int split_pick = 0;
   bool own_launch = false;        // batched plan: a plain launch of its own inside the
                                   // graph instead of items of the persistent launch
 };
@@ -182,12 +185,16 @@ double split_us(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int pha
 // Time split of an untuned array: the workgroups per channel group (and
 // phase) with the least modelled time.
 int choose_split(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int phases) {
+  if (rows == s.split_rows && s.k == s.split_kernel) return s.split_pick;
   double best = 0;
   int pick = 1;
   for (int ts = 1; ts <= 64 && (ts == 1 || rows / ts >= 64); ++ts) {
     const double us = split_us(p, s, rows, phases, ts);
     if (best == 0 || us < best) best = us, pick = ts;
   }
+  s.split_rows = rows;
+  s.split_kernel = s.k;
+  s.split_pick = pick;
   return pick;
 }
 
@@ -307,6 +314,7 @@ int init_slot(xeng_plan_t* p, ArrayState& s, const xeng_array_desc& d) {
     s.part_chunks = INT_MAX;
     const Grid g = grid_for(p, s, d.max_time_per_call);
     s.part_chunks = g.parts && g.dim.y * s.acc_bytes <= MAX_PART_BYTES ? (int)g.dim.y : 0;
+    s.split_rows = -1;  // (that was with room for any number)
   }
   const size_t acc_room = s.part_chunks ? (s.acc_bytes + 255) / 256 * 256 : s.acc_bytes;
   hipError_t e = hipMalloc(&s.acc, acc_room + s.part_chunks * s.acc_bytes);

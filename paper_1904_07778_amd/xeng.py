@@ -129,6 +129,13 @@ def _ptr(x) -> int | None:
     raise TypeError(f"cannot take the address of {type(x).__name__}")
 
 
+def _current_stream():
+    """torch.cuda.current_stream(), by device index (2 us less per call than
+    finding the index from None)."""
+    import torch
+    return torch.cuda.current_stream(torch.cuda.current_device())
+
+
 # ----------------------------------------------------------- raw C entry points
 def xeng_plan(arrays: Sequence[tuple[int, int, int]], flags: int = 0, stream=None) -> int:
     """arrays: (n_inputs, n_chans, max_time_per_call) per array; stream: torch
@@ -261,7 +268,7 @@ def requantize(words, gains, out=None, stream=None):
         out = torch.empty((T, F, N), dtype=torch.uint8, device=words.device)
     elif out.shape != words.shape or out.dtype != torch.uint8 or not out.is_contiguous():
         raise ValueError("out must be a contiguous uint8 tensor shaped like words")
-    stream = stream if stream is not None else torch.cuda.current_stream()
+    stream = stream if stream is not None else _current_stream()
     xeng_requantize(words, gains, out, T, F, N, stream)
     return out
 
@@ -285,7 +292,7 @@ def eq_update(vis, n_integrated: int, gains, target_rms: float = 2.5, out=None, 
         raise ValueError("gains must be a contiguous 4-byte CUDA tensor")
     tx = int(round(target_rms * 16))
     out = torch.empty_like(gains) if out is None else out
-    stream = stream if stream is not None else torch.cuda.current_stream()
+    stream = stream if stream is not None else _current_stream()
     xeng_eq_update(vis, n_integrated, gains, out, F, N, tx, stream)
     return out
 
@@ -309,7 +316,7 @@ def ingest(packets, mcnt0: int, n_blocks: int, n_boards: int, n_chans: int, xid:
     if tuple(out.shape) != shape or out.dtype != torch.uint8 or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous uint8 tensor {shape}")
     index = torch.empty((n_blocks, n_boards), dtype=torch.int32, device=packets.device)
-    stream = stream if stream is not None else torch.cuda.current_stream()
+    stream = stream if stream is not None else _current_stream()
     xeng_ingest(packets if packets.shape[0] else None, packets.shape[0], packets.shape[1], mcnt0, n_blocks,
                 n_boards, n_chans, xid, index, out, stream)
     return out, index
@@ -340,12 +347,32 @@ def channelise(adc, n_chans: int, out=None, tables=None, stream=None):
     if tables is None:
         tables = torch.empty(int(_lib.xeng_channelise_table_floats(n_chans)), dtype=torch.float32,
                              device=adc.device)
-    stream = stream if stream is not None else torch.cuda.current_stream()
+    stream = stream if stream is not None else _current_stream()
     xeng_channelise(adc, S_in, N, n_chans, out, tables, stream)
     return out
 
 
 # ------------------------------------------------------------ tensor wrapper
+_dtypes = {}
+
+
+def _uint8():
+    """torch.uint8, without importing torch with this module."""
+    d = _dtypes.get("uint8")
+    if d is None:
+        import torch
+        d = _dtypes["uint8"] = torch.uint8
+    return d
+
+
+def _int32():
+    d = _dtypes.get("int32")
+    if d is None:
+        import torch
+        d = _dtypes["int32"] = torch.int32
+    return d
+
+
 @dataclass
 class ArraySpec:
     n_inputs: int
@@ -355,6 +382,19 @@ class ArraySpec:
     @property
     def nbl(self) -> int:
         return self.n_inputs * (self.n_inputs + 1) // 2
+
+
+class _Call:
+    """The C argument arrays of a plan's calls, kept between them: one entry
+    per slot.  (A plan is used by one thread at a time, and the library reads
+    its arguments during the call only.)"""
+
+    def __init__(self, n: int):
+        self.n = n
+        self.voltages = (_P * n)()
+        self.n_time = (ctypes.c_int64 * n)()
+        self.dst = (_P * n)()
+        self.n_integrated = (ctypes.c_int64 * n)()
 
 
 class Plan:
@@ -375,6 +415,7 @@ class Plan:
         self.specs: list[ArraySpec | None] = [ArraySpec(*a) for a in arrays]
         self.stream = stream if stream is not None else torch.cuda.Stream()
         self.batched = batch or len(self.specs) > 1
+        self._call = _Call(0)
         self.handle = None
         self.handle = xeng_plan([(s.n_inputs, s.n_chans, s.max_time_per_call) for s in self.specs],
                                 XENG_PLAN_BATCH if batch else 0, self.stream.cuda_stream)
@@ -412,83 +453,93 @@ class Plan:
         xeng_detach(self.handle, index)
         self.specs[index] = None
 
-    def _after_caller(self, tensors=()):
-        """Order the engine's stream after the caller's current stream.  When
-        the caller already runs on the engine's stream this is stream order
-        and nothing is inserted: a wait across two streams costs a queue
-        hand-off of tens of microseconds per call on the device."""
-        import torch
-        cur = torch.cuda.current_stream()
+    def _after_caller(self, tensors=()) -> bool:
+        """Order the engine's stream after the caller's current stream; True if
+        they are two streams.  When the caller already runs on the engine's
+        stream this is stream order and nothing is inserted: a wait across two
+        streams costs a queue hand-off of tens of microseconds per call on the
+        device."""
+        cur = _current_stream()
         if cur == self.stream:
-            return
+            return False
         self.stream.wait_stream(cur)
         for t in tensors:
             if t is not None:
                 t.record_stream(self.stream)
+        return True
 
     def _caller_after(self):
         """Order the caller's current stream after the engine's stream."""
-        import torch
-        cur = torch.cuda.current_stream()
+        cur = _current_stream()
         if cur != self.stream:
             cur.wait_stream(self.stream)
 
-    def _marshal(self, voltages):
-        import torch
-        if len(voltages) != len(self.specs):
+    def _marshal(self, voltages) -> _Call:
+        """Check the voltage blocks and put their pointers and lengths into
+        the plan's argument arrays."""
+        specs = self.specs
+        if len(voltages) != len(specs):
             raise ValueError("one voltage tensor (or None) per slot")
-        ptrs, ts = [], []
-        for v, s in zip(voltages, self.specs):
+        call = self._call
+        if call.n != len(specs):
+            call = self._call = _Call(len(specs))
+        for a, (v, s) in enumerate(zip(voltages, specs)):
             if v is None:
-                ptrs.append(None)
-                ts.append(0)
+                call.voltages[a] = None
+                call.n_time[a] = 0
                 continue
             if s is None:
                 raise ValueError("voltages given for a free slot")
-            if v.dtype != torch.uint8 or not v.is_cuda or not v.is_contiguous():
+            if v.dtype != _uint8() or not v.is_cuda or not v.is_contiguous():
                 raise ValueError("voltages must be contiguous uint8 device tensors")
-            if v.dim() != 3 or v.shape[1] != s.n_chans or v.shape[2] != s.n_inputs:
-                raise ValueError(f"voltage block {tuple(v.shape)} does not match [T, {s.n_chans}, {s.n_inputs}]")
-            ptrs.append(v)
-            ts.append(v.shape[0])
-        return ptrs, ts
+            shape = v.shape
+            if len(shape) != 3 or shape[1] != s.n_chans or shape[2] != s.n_inputs:
+                raise ValueError(f"voltage block {tuple(shape)} does not match [T, {s.n_chans}, {s.n_inputs}]")
+            call.voltages[a] = v.data_ptr()
+            call.n_time[a] = shape[0]
+        return call
 
     def correlate(self, voltages) -> None:
         """voltages: one uint8 CUDA tensor [T, F, N] per slot (None skips)."""
-        import torch
-        ptrs, ts = self._marshal(voltages)
-        self._after_caller(ptrs)
-        xeng_correlate(self.handle, ptrs, ts)
+        call = self._marshal(voltages)
+        self._after_caller(voltages)
+        _check(_lib.xeng_correlate(self.handle, call.voltages, call.n_time), self.handle)
 
     def correlate_dump(self, voltages, out=None):
         """Integrate one block per slot and dump every slot given a block into
         out (device int32 [F, nbl, 2] tensors, made if None); returns (out,
         n_integrated) like dump().  Slots whose voltage entry is None keep
         integrating and get None in out."""
-        import torch
-        ptrs, ts = self._marshal(voltages)
+        call = self._marshal(voltages)
         if out is None:
             out = [None if v is None else self.new_output(a) for a, v in enumerate(voltages)]
         if len(out) != len(self.specs):
             raise ValueError("one output tensor (or None) per slot")
         for a, (o, s) in enumerate(zip(out, self.specs)):
+            call.n_integrated[a] = 0
             if o is None:
+                call.dst[a] = None
                 continue
-            if (not o.is_cuda or o.dtype != torch.int32 or not o.is_contiguous()
+            if (not o.is_cuda or o.dtype != _int32() or not o.is_contiguous()
                     or tuple(o.shape) != (s.n_chans, s.nbl, 2)):
                 raise ValueError(f"out[{a}] must be a contiguous int32 CUDA tensor [F, nbl, 2]")
-        self._after_caller(ptrs)
-        n = xeng_correlate_dump(self.handle, ptrs, ts, out)
-        self._caller_after()
-        return out, n
+            call.dst[a] = o.data_ptr()
+        waits = self._after_caller(voltages)
+        _check(_lib.xeng_correlate_dump(self.handle, call.voltages, call.n_time, call.dst, call.n_integrated),
+               self.handle)
+        if waits:
+            self._caller_after()
+        return out, list(call.n_integrated)
 
     def autotune(self, voltages, reps: int = 3) -> float:
         """Pick launch shapes by timing them on these inputs (accumulators must
         be freshly dumped; they are zero afterwards).  Returns ms per call."""
         import torch
-        ptrs, ts = self._marshal(voltages)
+        call = self._marshal(voltages)
         self._after_caller()
-        return xeng_autotune(self.handle, ptrs, ts, reps)
+        best = ctypes.c_float()
+        _check(_lib.xeng_autotune(self.handle, call.voltages, call.n_time, reps, ctypes.byref(best)), self.handle)
+        return best.value
 
     def stats(self) -> dict:
         """Counters since the plan was made (calls, launches, samples, cmacs,
