@@ -81,7 +81,7 @@ enum {
  *              With one array (and no flag) this is the plain per-dump
  *              engine: one kernel launch per xeng_correlate.  Otherwise the
  *              plan is batched: every xeng_correlate runs the work of all its
- *              arrays as one persistent launch over a work list of (array,
+ *              arrays as one launch over a work list of (array,
  *              channel group, time chunk) items, recorded into a hipGraph
  *              (Sec. 2: each X node takes a band of channels; Sec. 2.2: one
  *              GPU core per band - here many bands of many arrays share one
@@ -181,7 +181,7 @@ int xeng_detach(xeng_plan_t *p, int32_t index);
 /* Counters of a plan since it was made (xeng_stats). */
 typedef struct {
     int64_t calls;      /* xeng_correlate calls that did work                     */
-    int64_t launches;   /* kernel launches (plain, or persistent batch launches)   */
+    int64_t launches;   /* kernel launches (plain, or batch launches)              */
     int64_t samples;    /* time samples integrated, summed over arrays             */
     int64_t cmacs;      /* useful complex MACs: samples x F x N(N+1)/2, summed     */
     int64_t bytes_in;   /* voltage bytes consumed                                  */
@@ -213,9 +213,9 @@ int64_t xeng_accumulator_bytes(int32_t n_inputs, int32_t n_chans);
  *   d_voltages, n_time  one call's arguments, as for xeng_correlate.
  *   reps                calls timed per candidate (>= 1).
  *   best_ms             optional out: mean time of one call with the choice.
- * Batched plan: the work-item granularity of the persistent launch (about
+ * Batched plan: the work-item granularity of the batch launch (about
  * 1, 2, 4 or 8 items per compute unit; items are cut along time), then per
- * array, largest first, whether it runs as items of the persistent launch
+ * array, largest first, whether it runs as items of the batch launch
  * (16-row tiles) or as a plain launch of its own inside the same graph, with
  * the tile shape and time split that suit it.  Plain plan, per array: the
  * tile shape (16-row tiles of the 16x16x64 ring kernel, 32-row tiles of the

@@ -1,14 +1,22 @@
-// batch.hpp - one persistent launch over the X-engine work of many arrays.
+// batch.hpp - one launch over the X-engine work of many arrays.
 //
 // The paper gives each GPU of an X node a band of channels (Sec. 2, Sec. 2.2)
 // and runs one kernel per band.  Here many independent arrays, of uneven
 // input counts, channel counts and integration lengths, share one GPU: their
-// work is cut into items (array, channel group, time chunk) and a single
-// persistent grid of one workgroup per compute unit pulls items from work
-// queues until all are done.  Every item runs the same per-wave body as the
-// plain launch of the 16-row-tile kernel (x16::wave_main) with the launch
-// shape compiled for its N, so the sums are bit-identical to the plain
-// engine's.
+// work is cut into items (array, channel group, time chunk) and the
+// workgroups of a single grid take items from work queues.  Every item runs
+// the same per-wave body as the plain launch of the 16-row-tile kernel
+// (x16::wave_main) with the launch shape compiled for its N, so the sums are
+// bit-identical to the plain engine's.
+//
+// The host launches one workgroup per item (per_wg = 1), which the hardware
+// starts as CUs become free.  With one workgroup per CU that takes items
+// until all are done, the next item's ring loads share the memory counter
+// with the last item's stores and wait for them, where a new workgroup starts
+// while they drain: N = 192, F = 1024, T = 1024, adding, 169 us per call in
+// that form and 156 in this one; the four serving arrays 219 and 213, and 187
+// and 175 storing (230 and 197 with a device-scope fence per wave at the end
+// of each workgroup, which wrote back the L2 and is not needed).
 //
 // Queues.  There is one queue per XCD (workgroup w runs on XCD w % 8).  Each
 // array's channel groups are cut into 8 contiguous ranges, one per queue;
@@ -16,7 +24,7 @@
 // so the workgroups of one XCD work on neighbouring channels at the same
 // time and share the 128-byte lines that straddle two channels in its L2.
 // Arrays are listed in the order the host chose (longest items first).  A
-// workgroup whose queue is empty takes items from the next queues in turn.
+// workgroup whose queue is empty takes an item from the next queues in turn.
 //
 // Counters.  counters[0..7] are the queue heads and counters[8] counts the
 // workgroups that have finished; all are zero before a launch.  The last
@@ -43,6 +51,7 @@ struct Params {
   int32_t nchunks[MAX_ARRAYS];   // time chunks
   int32_t n_arrays;
   int32_t* counters;             // [QUEUES + 1], zero between launches
+  int32_t per_wg;                // items a workgroup takes at most
 };
 
 // Channel groups [begin, end) of queue x for an array with g groups.

@@ -1,4 +1,4 @@
-// The persistent batch kernel (batch.hpp): all supported N in one function.
+// The batch kernel (batch.hpp): all supported N in one function.
 #include "batch.hpp"
 
 namespace xeng {
@@ -13,6 +13,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1))) vo
   __shared__ __attribute__((aligned(1024))) uint8_t lds[lds_bytes()];
   __shared__ int item_slot;
   const int home = blockIdx.x % QUEUES;
+  int left = p.per_wg;
 
   // items of array k in queue x
   auto count = [&](int k, int x) {
@@ -47,12 +48,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1))) vo
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     run_if<16>(a.N, a, lds, g0 + q % ng, q / ng, tid);
+    if (--left == 0) break;
     __syncthreads();  // the item's last LDS reads are done before the next item's loads land
   }
 
-  // The last workgroup out clears the counters for the next launch.
-  __threadfence();
-  __syncthreads();
+  // The last workgroup out clears the counters for the next launch.  (Thread
+  // 0 alone touches them, and had the answers to its earlier atomics; no
+  // fence, which would write back the L2 once per wave.)
   if (threadIdx.x == 0) {
     const int done = atomicAdd(&p.counters[QUEUES], 1);
     if (done == (int)gridDim.x - 1) {

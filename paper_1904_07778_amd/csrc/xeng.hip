@@ -4,7 +4,7 @@
 // [F][nbl][2], the number of samples integrated since the last dump, and the
 // kernel configuration chosen for its N.  xeng_correlate validates, applies
 // the overflow guard and launches: one launch per array in a plain plan, one
-// captured graph around the persistent batch kernel in a batched plan.
+// captured graph around the batch kernel in a batched plan.
 // xeng_dump copies the accumulators out and clears them on the plan's
 // stream.  Slots can be attached and detached between calls (admission in a
 // serving loop).
@@ -52,7 +52,7 @@ struct ArrayState {
   mutable int64_t split_rows = -1;                   // the kernel and a call's rows alone
   mutable int split_pick = 0;
   bool own_launch = false;        // batched plan: a plain launch of its own inside the
-                                  // graph instead of items of the persistent launch
+                                  // graph instead of items of the batch launch
 };
 
 // ---- tuning cache: the launch shapes the autotuner picked, by GPU
@@ -104,8 +104,8 @@ struct xeng_plan_s {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   bool dead = false;
-  bool batched = false;   // calls go through the persistent batch launch
-  int batch_split = 2;    // batch: about batch_split items per workgroup
+  bool batched = false;   // calls go through the batch launch
+  int batch_split = 0;    // batch: cut items to about batch_split per CU; 0: modelled
   std::vector<ArrayState> arrays;
   int32_t* counters = nullptr;  // batch queue heads, zero between launches
   // Ring of instantiated graphs of batched calls, each with the event of its
@@ -142,20 +142,6 @@ bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u
 
 int64_t nbl_of(int32_t n) { return (int64_t)n * (n + 1) / 2; }
 
-constexpr double HBM_BYTES_PER_CYCLE = 13.0;  // 8 TB/s over 256 CUs at 2.4 GHz
-
-double cycles_per_sample(const KernelInfo* k, int32_t n) {
-  // units (real or imaginary product of one tile pair) per channel; a 32-row
-  // unit takes 32 MFMA cycles per 16 samples, a 16-row unit 16 cycles per 32
-  // samples; a workgroup's four SIMDs share its CPW channels' units
-  const int nt = (n + k->tile_rows - 1) / k->tile_rows;
-  const double per_unit = k->tile_rows == 32 ? 2.0 : 0.5;
-  const double mfma = (double)nt * (nt + 1) * per_unit * k->cpw / 4.0;
-  const double hbm = (double)k->cpw * n / HBM_BYTES_PER_CYCLE;
-  return mfma > hbm ? mfma : hbm;
-}
-
-
 // Modelled time of a call of the 16-row ring kernel in ts time chunks per
 // channel group and phase: rounds of workgroups over the CUs, each a start
 // (launch or hand-over, ring fill, epilogue) plus its rows.  A workgroup's
@@ -169,13 +155,16 @@ double cycles_per_sample(const KernelInfo* k, int32_t n) {
 // chunks 80, 36, 27, 30 (105 with atomics in 16); 192x35x6736 in 1, 4, 8
 // chunks 82, 35, 45; 96x200x4096 in 1, 4, 8 67, 37, 51; 32x64x4096 in 1, 4,
 // 8, 16 25, 16, 12, 13; 128x64x2048 in 1, 2, 4 18, 20, 22.
+double row_ns(const KernelInfo* k) {
+  const double mfma = k->nt * (k->nt + 1) / (double)k->w / 2.0 / 2.0;  // 16 cycles per unit and 32 rows
+  return std::max({1.2 * mfma + 1.0, k->cpw * 16.0 * k->nt / 25.0, 4.0});
+}
+
 double split_us(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int phases, int ts) {
   const int64_t groups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
   const int64_t wgs = groups * phases * ts;
-  const double mfma_ns = s.k->nt * (s.k->nt + 1) / (double)s.k->w / 2.0 / 2.0;  // per row: 16 cycles per 32
-  const double row_ns = std::max({1.2 * mfma_ns + 1.0, s.k->cpw * 16.0 * s.k->nt / 25.0, 4.0});
   const double rounds = (double)((wgs + p->n_cu - 1) / p->n_cu);
-  const double us = rounds * (4.0 + (double)((rows + ts - 1) / ts) * row_ns * 1e-3);
+  const double us = rounds * (4.0 + (double)((rows + ts - 1) / ts) * row_ns(s.k) * 1e-3);
   const int n = ts * phases;
   if (n == 1) return us;
   const double acc = (double)s.acc_bytes;
@@ -402,24 +391,53 @@ int launch_plain(xeng_plan_t* p, ArrayState& s, const uint8_t* v, int64_t T) {
 }
 
 // Batched call.  Arrays whose N the batch kernel covers become items of one
-// persistent launch (several when there are more than batch::MAX_ARRAYS);
-// the rest get their plain launch.  Per array the time range is cut into
-// chunks so that the items come to about batch_split per workgroup, from a
-// cost model of the kernel (the larger of its MFMA cycles and its HBM bytes
-// per sample, plus a fixed start-up cost per item); arrays are queued longest
-// item first.
-constexpr double ITEM_START_CYCLES = 4000.0;  // ring fill and epilogue of one item
+// launch (several when there are more than batch::MAX_ARRAYS); the rest get
+// their plain launch.  Per array the time range is cut into chunks so that
+// the items come to about `split` per CU, by the modelled time of a row
+// (row_ns) and a start per item; arrays are queued longest item first.
+// Untuned plans take the split with the least modelled time: the work spread
+// over the CUs, half of the longest item (what the CUs wait for at the end)
+// and the atomic adds of the arrays that are cut.  (96x1024, 32x1024 and
+// 32x256, 1024 samples: 68 us per call uncut, 188 cut for two items per CU.)
+constexpr double ITEM_START_US = 4.0;
+
 struct BatchEntry {
   int32_t a;
   int32_t ngroups, nchunks;
   int64_t t_chunk;
-  double item_cycles;
+  double item_us;
 };
+
+// Cut the items to about split per CU (0: not at all, but for the longest
+// range a workgroup takes); returns the modelled time of the call.
+double cut_items(const xeng_plan_t* p, const int64_t* n_time, int split, std::vector<BatchEntry>& items) {
+  double total = 0, longest = 0, adds = 0;
+  for (const BatchEntry& b : items)
+    total += b.ngroups * (n_time[b.a] * row_ns(p->arrays[b.a].k) * 1e-3 + ITEM_START_US);
+  const double target = split ? total / ((double)split * p->n_cu) : 1e30;
+  total = 0;
+  for (BatchEntry& b : items) {
+    const ArrayState& s = p->arrays[b.a];
+    const int64_t T = n_time[b.a];
+    const double full = T * row_ns(s.k) * 1e-3;
+    int64_t nc = (int64_t)std::ceil(full / std::max(target, 1.0));
+    nc = std::max<int64_t>(1, std::min<int64_t>(nc, T / 256));
+    nc = std::max<int64_t>(nc, (T + s.k->max_t_per_wg - 1) / s.k->max_t_per_wg);
+    int64_t tc = (T + nc - 1) / nc;
+    tc = (tc + xeng::KS - 1) / xeng::KS * xeng::KS;
+    b.t_chunk = tc;
+    b.nchunks = (int32_t)((T + tc - 1) / tc);
+    b.item_us = tc * row_ns(s.k) * 1e-3 + ITEM_START_US;
+    total += b.ngroups * b.nchunks * b.item_us;
+    longest = std::max(longest, b.item_us);
+    if (b.nchunks > 1) adds += 2.0 + b.nchunks * (double)s.acc_bytes / 4.0 / 115e3;
+  }
+  return std::max(total / p->n_cu, longest / 2) + longest / 2 + adds;
+}
 
 int record_batched(xeng_plan_t* p, const uint8_t* const* v, const int64_t* n_time) {
   std::vector<BatchEntry> items;
   std::vector<int32_t> others;
-  double total = 0;
   for (int32_t a = 0; a < (int32_t)p->arrays.size(); ++a) {
     const ArrayState& s = p->arrays[a];
     if (!s.active || n_time[a] == 0) continue;
@@ -430,25 +448,19 @@ int record_batched(xeng_plan_t* p, const uint8_t* const* v, const int64_t* n_tim
     BatchEntry b{};
     b.a = a;
     b.ngroups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
-    total += (double)b.ngroups * (n_time[a] * cycles_per_sample(s.k, s.d.n_inputs) + ITEM_START_CYCLES);
     items.push_back(b);
   }
-  const double target = total / ((double)std::max(1, p->batch_split) * p->n_cu);
-  for (BatchEntry& b : items) {
-    const ArrayState& s = p->arrays[b.a];
-    const int64_t T = n_time[b.a];
-    const double full = T * cycles_per_sample(s.k, s.d.n_inputs);
-    int64_t nc = (int64_t)std::ceil(full / std::max(target, 1.0));
-    nc = std::max<int64_t>(1, std::min<int64_t>(nc, T / 256));
-    nc = std::max<int64_t>(nc, (T + s.k->max_t_per_wg - 1) / s.k->max_t_per_wg);
-    int64_t tc = (T + nc - 1) / nc;
-    tc = (tc + xeng::KS - 1) / xeng::KS * xeng::KS;
-    b.t_chunk = tc;
-    b.nchunks = (int32_t)((T + tc - 1) / tc);
-    b.item_cycles = tc * cycles_per_sample(s.k, s.d.n_inputs) + ITEM_START_CYCLES;
+  int split = p->batch_split;
+  if (split == 0) {
+    double best = cut_items(p, n_time, 0, items);
+    for (int sp : {1, 2, 4, 8}) {
+      const double us = cut_items(p, n_time, sp, items);
+      if (us < best) best = us, split = sp;
+    }
   }
+  cut_items(p, n_time, split, items);
   std::stable_sort(items.begin(), items.end(),
-                   [](const BatchEntry& x, const BatchEntry& y) { return x.item_cycles > y.item_cycles; });
+                   [](const BatchEntry& x, const BatchEntry& y) { return x.item_us > y.item_us; });
   std::vector<ArrayState*> to_init;
   for (const BatchEntry& b : items) {
     ArrayState& s = p->arrays[b.a];
@@ -474,7 +486,9 @@ int record_batched(xeng_plan_t* p, const uint8_t* const* v, const int64_t* n_tim
       bp.nchunks[k] = b.nchunks;
       n_items += (int64_t)b.ngroups * b.nchunks;
     }
-    const int grid = (int)std::min<int64_t>(p->n_cu, n_items);
+    if (n_items > INT_MAX) return fail(p, XENG_EINVAL, "batch of %lld items", (long long)n_items);
+    bp.per_wg = 1;
+    const int grid = (int)n_items;
     ++p->stats.launches;
     if (p->trace)
       fprintf(stderr, "xeng: plan %p batch launch arrays=%d items=%lld grid=%d\n", (void*)p, bp.n_arrays,
@@ -835,7 +849,7 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
 
   float best = 0;
   if (p->batched) {
-    // work-item granularity of the persistent launch
+    // work-item granularity of the batch launch
     const int cand[] = {1, 2, 4, 8};
     int pick = p->batch_split;
     for (int i = 0; i < 4 && st == XENG_OK; ++i) {
@@ -848,7 +862,7 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
       }
     }
     p->batch_split = pick;
-    // Per array, largest work first: items of the persistent launch (16-row
+    // Per array, largest work first: items of the batch launch (16-row
     // tiles), or a plain launch of its own inside the same graph with the
     // tile shape and time split that suit it best; kept when the whole call
     // gets faster by more than 1%.
