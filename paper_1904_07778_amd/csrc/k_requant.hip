@@ -93,7 +93,10 @@ __global__ __launch_bounds__(THREADS) void requant8(const uint64_t* __restrict__
   }
 }
 
-// General path: any F*N and alignment (8-byte words, 4-byte gains).
+// General path: any F*N and alignment (8-byte words, 4-byte gains).  A
+// thread takes its rows four at a time, the four loads in flight together:
+// one after the other, each 8-byte load waited for the one before it.
+constexpr int ROWS1 = 4;
 __global__ __launch_bounds__(THREADS) void requant1(const uint64_t* __restrict__ w,
                                                     const uint32_t* __restrict__ gains,
                                                     uint8_t* __restrict__ out, int64_t T, int64_t fn, int rows) {
@@ -102,7 +105,14 @@ __global__ __launch_bounds__(THREADS) void requant1(const uint64_t* __restrict__
   const int64_t t0 = (int64_t)blockIdx.y * rows;
   const int64_t t1 = min(T, t0 + rows);
   const int g = gains[x] & 0x3FFFF;
-  for (int64_t t = t0; t < t1; ++t) out[t * fn + x] = (uint8_t)byte_of(w[t * fn + x], g);
+  for (int64_t t = t0; t < t1; t += ROWS1) {
+    uint64_t v[ROWS1];
+#pragma unroll
+    for (int k = 0; k < ROWS1; ++k) v[k] = w[min(t + k, t1 - 1) * fn + x];
+#pragma unroll
+    for (int k = 0; k < ROWS1; ++k)
+      if (t + k < t1) out[(t + k) * fn + x] = (uint8_t)byte_of(v[k], g);
+  }
 }
 
 // Gain update from the autocorrelations (Eq. 3): one thread per (channel,
@@ -176,11 +186,13 @@ extern "C" int xeng_requantize(const uint64_t* d_words, const uint32_t* d_gains,
   if (gx > 2147483647LL || (n_time + xeng::MAX_ROWS - 1) / xeng::MAX_ROWS > 2147483647LL) return XENG_EINVAL;
   // Rows per thread: as many as keep the gains in registers longest while the
   // grid still fills every wave slot (8 workgroups on each of 256 CUs): a
-  // thread's rows go one after the other, each a memory round trip.  (N = 32,
-  // F = 512, T = 512: 32 us in 256 workgroups of 16 rows, 17 in 2048 of 2; N = 158, F = 77,
-  // T = 134: 30 and 6.)
+  // thread's rows go one after the other (four by four in the general path),
+  // each a memory round trip.  (N = 32, F = 512, T = 512: 32 us in 256
+  // workgroups of 16 rows, 17 in 2048 of 2; N = 158, F = 77, T = 134: 30 and 6;
+  // general path, N = 91, F = 754, T = 23: 29 and 6.)
   const int64_t room = n_time * gx / (8 * 256);
-  const int rows = (int)(room < 1 ? 1 : room > xeng::MAX_ROWS ? xeng::MAX_ROWS : room);
+  int rows = (int)(room < 1 ? 1 : room > xeng::MAX_ROWS ? xeng::MAX_ROWS : room);
+  if (!fast) rows = rows < xeng::ROWS1 ? xeng::ROWS1 : rows / xeng::ROWS1 * xeng::ROWS1;
   const int64_t ty = (n_time + rows - 1) / rows;
   const dim3 grid((unsigned)gx, (unsigned)ty);
   if (fast)
