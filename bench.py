@@ -22,7 +22,7 @@ of the same workload.
 
 Other workloads (one JSON line each, same keys plus a comparison):
   --workload batch    12 arrays of uneven N, F, T (seeded): one batched
-                      correlate-and-dump call (persistent launch in a captured
+                      correlate-and-dump call (one launch in a captured
                       graph) per step, against 12 plain correlate-and-dump
                       calls on the same stream; both autotuned first; outputs
                       compared bit for bit.
@@ -128,7 +128,7 @@ def tuned_choices(shapes, batched: bool) -> str:
                    f"N={n}: {KIND_NAMES.get(c[0], c[0])} split {c[1]}{' own launch' if c[2] else ''}")
     plan = table.get((1, 0, 0, _bucket(len(shapes)))) if batched else None
     if plan is not None:
-        out.append(f"persistent launch: {plan[1]} items per workgroup")
+        out.append(f"batch launch: {plan[1]} items per CU")
     return "; ".join(out)
 
 

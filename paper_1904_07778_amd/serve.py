@@ -24,7 +24,7 @@ Here the same chain serves several independent sub-arrays at once on one GPU:
   blocks a slot has ready (consecutive in its ring, up to its next dump
   boundary) go in as one time range, so queued blocks coalesce into fewer,
   longer items and fewer accumulator passes.  The call is one captured graph
-  launch of the persistent batch kernel; work of different sub-arrays
+  launch of the batch kernel; work of different sub-arrays
   overlaps on the device.
 * A slot whose integration is complete is dumped by the dump kernel into a
   device buffer and copied to pinned host memory on a copy stream; its

@@ -405,7 +405,7 @@ class Plan:
 
     def __init__(self, arrays: Sequence[tuple[int, int, int]], stream=None, batch: bool = False):
         """stream: a torch.cuda.Stream the engine runs on; by default a new one.
-        batch: force the batched form (persistent graph launch) even for one or
+        batch: force the batched form (one graph launch) even for one or
         zero arrays; it is implied by more than one array.
         correlate() orders the engine after the caller's current stream, and
         dump() orders the caller's current stream after the engine; a caller
