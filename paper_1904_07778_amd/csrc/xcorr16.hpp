@@ -288,10 +288,12 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
     // site (the compiler cannot prove the sites distinct, and otherwise waits
     // for each load in turn; N=192: 0.51 against 0.58 ms per launch).
     constexpr int CH = 16;
+    const int32_t* prevf = accf + a.prev_off;
     sfor<0, (NU + CH - 1) / CH>([&](auto c) {
       constexpr int u0 = decltype(c)::value * CH, u1 = u0 + CH < NU ? u0 + CH : NU;
       v2i prev[CH][4];
-      // calls body(pair, im, dst, j, un) for site (u, v) when this lane holds one
+      // calls body(pair, im, at, jp, un) for site (u, v) when this lane holds one:
+      // at is the baseline's place from accf, jp the column's position
       auto site = [&](auto u, auto v, auto body) {
         constexpr int I = plan.uI[WC][u], J = plan.uJ[WC][u], IM = plan.uIm[WC][u];
         constexpr int un = u + 1 < NU ? u + 1 : u, up = u > 0 ? u - 1 : 0;
@@ -303,23 +305,23 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
           const int i = 16 * I + mb + v - s;
           if (baseline(std::integral_constant<int, I>{}, std::integral_constant<int, J>{}, i, j))
             body(std::integral_constant<bool, PAIR>{}, std::integral_constant<int, IM>{},
-                 accf + (i * (i + 1) / 2 + j) * 2, 16 * J + n, un);
+                 (i * (i + 1) / 2 + j) * 2, 16 * J + n, un);
         }
       };
       sfor<u0, u1>([&](auto u) {
         sfor<0, 4>([&](auto v) {
-          site(u, v, [&](auto pair, auto im, int32_t* dst, int, int) {
+          site(u, v, [&](auto pair, auto im, int at, int, int) {
             if constexpr (pair.value)
-              prev[u - u0][v] = *reinterpret_cast<const v2i*>(dst + a.prev_off);
+              prev[u - u0][v] = *reinterpret_cast<const v2i*>(prevf + at);
             else
-              prev[u - u0][v][0] = dst[a.prev_off + im.value];
+              prev[u - u0][v][0] = prevf[at + im.value];
           });
         });
       });
       sfor<u0, u1>([&](auto u) {
         constexpr int I = plan.uI[WC][u];
         sfor<0, 4>([&](auto v) {
-          site(u, v, [&](auto pair, auto im, int32_t* dst, int jp, int un) {
+          site(u, v, [&](auto pair, auto im, int at, int jp, int un) {
             auto im_of = [&](int32_t x) {
               if constexpr (QC)
                 return (drow[16 * I + mb + (int)v] - x) >> 8;
@@ -329,9 +331,9 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
             const int32_t x = acc_read(acc[u], v);
             if constexpr (pair.value) {
               const int32_t y = acc_read(acc[un], v);
-              *reinterpret_cast<v2i*>(dst) = prev[u - u0][v] + v2i{x >> 8, im_of(y)};
+              *reinterpret_cast<v2i*>(accf + at) = prev[u - u0][v] + v2i{x >> 8, im_of(y)};
             } else {
-              dst[im.value] = prev[u - u0][v][0] + (im.value ? im_of(x) : x >> 8);
+              accf[at + im.value] = prev[u - u0][v][0] + (im.value ? im_of(x) : x >> 8);
             }
           });
         });

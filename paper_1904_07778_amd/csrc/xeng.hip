@@ -144,27 +144,43 @@ int64_t nbl_of(int32_t n) { return (int64_t)n * (n + 1) / 2; }
 
 // Modelled time of a call of the 16-row ring kernel in ts time chunks per
 // channel group and phase: rounds of workgroups over the CUs, each a start
-// (launch or hand-over, ring fill, epilogue) plus its rows.  A workgroup's
-// rows go at 1.2 times its matrix-core cycles (at 2 GHz), at no more than 25
-// bytes per ns (what one CU streams through its ring, also with most of the
-// chip idle: 24-28 measured for N = 32 .. 112) and at no less than 4 ns a
-// row.  Chunks are stored and summed by a second kernel: its launch, and the
+// (launch or hand-over, ring fill, epilogue) plus its rows.  A CU's rows go
+// at 1.2 times its matrix-core cycles (at 2 GHz) and at no more than 25 bytes
+// per ns (what one CU streams through its ring, also with most of the chip
+// idle: 24-28 measured for N = 32 .. 112); a workgroup alone takes 1 ns a row
+// longer and no less than 4 (N = 16, where four share a CU, gains by more of
+// them: F = 1024, T = 8192 36 us in one chunk, 32 in two).  Chunks are stored and summed by a second kernel: its launch, and the
 // store, the read and the sum at 6 bytes per ps (out of the caches mostly);
 // without room for them they are added atomically (115 G adds/s).  Measured
 // against it, kernel times in us for N x F x T: 100x64x4096 in 1, 4, 8, 16
 // chunks 80, 36, 27, 30 (105 with atomics in 16); 192x35x6736 in 1, 4, 8
 // chunks 82, 35, 45; 96x200x4096 in 1, 4, 8 67, 37, 51; 32x64x4096 in 1, 4,
 // 8, 16 25, 16, 12, 13; 128x64x2048 in 1, 2, 4 18, 20, 22.
-double row_ns(const KernelInfo* k) {
+// Nanoseconds per row of a workgroup's CU (busy), and of one workgroup alone.
+double busy_ns(const KernelInfo* k) {
   const double mfma = k->nt * (k->nt + 1) / (double)k->w / 2.0 / 2.0;  // 16 cycles per unit and 32 rows
-  return std::max({1.2 * mfma + 1.0, k->cpw * 16.0 * k->nt / 25.0, 4.0});
+  return std::max(1.2 * mfma, k->cpw * 16.0 * k->nt / 25.0);
+}
+double row_ns(const KernelInfo* k) {
+  const double mfma = k->nt * (k->nt + 1) / (double)k->w / 2.0 / 2.0;
+  return std::max({1.2 * mfma + 1.0, busy_ns(k), 4.0});
+}
+
+// Workgroups of a 16-row ring kernel that run on one CU together: by LDS, and
+// by registers (36 a lane at one tile, 84 at two, 224-248 at 8 tiles over four
+// waves, over 256 at any other count from 4 up).
+int together(const KernelInfo* k) {
+  const int regs = k->nt <= 3 ? 4 : k->nt == 8 ? 2 : 1;
+  return std::max(1, std::min(regs, 160 * 1024 / k->lds_bytes));
 }
 
 double split_us(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int phases, int ts) {
   const int64_t groups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
   const int64_t wgs = groups * phases * ts;
-  const double rounds = (double)((wgs + p->n_cu - 1) / p->n_cu);
-  const double us = rounds * (4.0 + (double)((rows + ts - 1) / ts) * row_ns(s.k) * 1e-3);
+  const int64_t per_cu = (wgs + p->n_cu - 1) / p->n_cu;
+  const int64_t rounds = (per_cu + together(s.k) - 1) / together(s.k);
+  const double rows_us = (double)((rows + ts - 1) / ts) * std::max(per_cu * busy_ns(s.k), rounds * row_ns(s.k)) * 1e-3;
+  const double us = rounds * 4.0 + rows_us;
   const int n = ts * phases;
   if (n == 1) return us;
   const double acc = (double)s.acc_bytes;
