@@ -468,9 +468,12 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
     // rows of this stage inside the range, clamped to [0, STAGE_T] in scalar
     // registers (a clamp in C becomes a vector med3 and a readfirstlane)
     int rows;
+    // (the limit is an immediate: %0 is written before the second instruction
+    // reads its operands, so a register for it could be %0 itself)
     asm("s_max_i32 %0, %1, 0\n\ts_min_i32 %0, %0, %2"
         : "=s"(rows)
-        : "s"(__builtin_amdgcn_readfirstlane(nt - st * STAGE_T)), "s"(STAGE_T));
+        : "s"(__builtin_amdgcn_readfirstlane(nt - st * STAGE_T)), "i"(STAGE_T)
+        : "scc");
     v4i rsrc;
     rsrc[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
     rsrc[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xFFFFu));
