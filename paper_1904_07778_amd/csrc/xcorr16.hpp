@@ -218,24 +218,34 @@ __device__ __forceinline__ void wait_vmcnt() {
 // the compiler does not make every later LDS read wait for all loads in
 // flight (the ring waits for each stage with s_waitcnt vmcnt + barrier).
 // No register is written; M0 is otherwise unused by this code.
+//
+// The compiler adds no wait states inside or in front of inline assembly, so
+// the ones that gfx950 needs stand in it: one between the write of M0 and the
+// load (s_nop 0), and five between a vector instruction that writes a
+// register of rsrc (v_readfirstlane) and the load.  The latter can only be
+// close before the first load of a stage (FIRST: s_nop 3).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+template <int OFF, bool FIRST>
 __device__ __forceinline__ void buf_dma16(v4i rsrc, uint32_t voff, uint32_t lds_base) {
   asm volatile(
-      "s_mov_b32 m0, %2\n\t"
+      "s_add_u32 m0, %2, %3\n\t"
+      "s_nop %4\n\t"
       "buffer_load_dwordx4 %0, %1, 0 offen lds"
       :
-      : "v"(voff), "s"(rsrc), "s"(lds_base)
-      : "memory", "m0");
+      : "v"(voff), "s"(rsrc), "s"(lds_base), "i"(OFF), "i"(FIRST ? 3 : 0)
+      : "memory", "m0", "scc");
 }
 // The same with 4 bytes per lane: a wave-wide 256-byte load.
+template <int OFF, bool FIRST>
 __device__ __forceinline__ void buf_dma4(v4i rsrc, uint32_t voff, uint32_t lds_base) {
   asm volatile(
-      "s_mov_b32 m0, %2\n\t"
+      "s_add_u32 m0, %2, %3\n\t"
+      "s_nop %4\n\t"
       "buffer_load_dword %0, %1, 0 offen lds"
       :
-      : "v"(voff), "s"(rsrc), "s"(lds_base)
-      : "memory", "m0");
+      : "v"(voff), "s"(rsrc), "s"(lds_base), "i"(OFF), "i"(FIRST ? 3 : 0)
+      : "memory", "m0", "scc");
 }
 #pragma clang diagnostic pop
 
@@ -481,20 +491,19 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
     rsrc[3] = 0x00020000;  // raw buffer, 32-bit data format
     const uint32_t base = ring_base + (uint32_t)((st % S) * C::STAGE_BYTES);
     if constexpr (LD == LD_DWORD) {
+      constexpr int ROW = C::RPP * 16;
+      const uint32_t row0 = base + wave * (C::ROWS_PER_WAVE * ROW);
       if (C::RPC * 4 == 64 || lane < C::RPC * 4) {
-#pragma unroll
-        for (int k = 0; k < C::ROWS_PER_WAVE; ++k)
-          buf_dma4(rsrc, voff[0] + (uint32_t)k * rs32, base + (wave * C::ROWS_PER_WAVE + k) * (C::RPP * 16));
+        sfor<0, C::ROWS_PER_WAVE>(
+            [&](auto k) { buf_dma4<k * ROW, k == 0>(rsrc, voff[0] + (uint32_t)k * rs32, row0); });
       }
-      return;
-    }
-#pragma unroll
-    for (int k = 0; k < LMAX; ++k) {
-      if constexpr (ONE) {
-        if (k < LW) buf_dma16(rsrc, voff[k], base + (LR + k * NLW) * 1024);
-      } else if (k < my_loads) {
-        buf_dma16(rsrc, voff[k], base + (wave + k * C::WAVES) * 1024);
-      }
+    } else if constexpr (ONE) {
+      sfor<0, LW>([&](auto k) { buf_dma16<(LR + k * NLW) * 1024, k == 0>(rsrc, voff[k], base); });
+    } else {
+      const uint32_t q0 = base + wave * 1024;
+      sfor<0, LMAX>([&](auto k) {
+        if (k < my_loads) buf_dma16<k * C::WAVES * 1024, k == 0>(rsrc, voff[k], q0);
+      });
     }
   };
 

@@ -143,12 +143,15 @@ __device__ __forceinline__ void wait_vmcnt() {
 // asm so the compiler does not make every later LDS read wait for all loads
 // in flight; the ring waits for each stage with s_waitcnt vmcnt + barrier.
 // No register is written.  M0 is otherwise unused by this code (checked in
-// the generated assembly), so clobbering it is safe.
+// the generated assembly), so clobbering it is safe.  The s_nop is the wait
+// state between a write of M0 and the load, which the compiler does not add
+// inside inline assembly.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_dma16(const uint8_t* gptr, uint32_t lds_base) {
   asm volatile(
       "s_mov_b32 m0, %1\n\t"
+      "s_nop 0\n\t"
       "global_load_lds_dwordx4 %0, off"
       :
       : "v"(gptr), "s"(lds_base)
