@@ -45,12 +45,13 @@ struct ArrayState {
   const int32_t* prev = nullptr;  // during xeng_correlate_dump: the earlier samples' sums,
                                   // while acc is the caller's destination
   const KernelInfo* k = nullptr;  // kernel of the plain launch
-  int split = 0;                  // plain launch: aim for split * n_cu workgroups; 0: choose_split
+  int split = 0;                  // plain launch: aim for split * n_cu workgroups; 0: modelled (choose)
+  const KernelInfo* other = nullptr;  // the kernel of the calls it is modelled faster for (choose)
   int32_t* part = nullptr;        // plain plan: room for part_chunks time chunks' sums, in
   int part_chunks = 0;            // the accumulator's allocation
-  mutable const KernelInfo* split_kernel = nullptr;  // choose_split's last pick: it depends on
-  mutable int64_t split_rows = -1;                   // the kernel and a call's rows alone
-  mutable int split_pick = 0;
+  mutable int64_t chosen_T = -1;  // choose's last pick, of calls of this length
+  mutable const KernelInfo* chosen_k = nullptr;
+  mutable int64_t chosen_ts = 0;
   bool own_launch = false;        // batched plan: a plain launch of its own inside the
                                   // graph instead of items of the batch launch
 };
@@ -59,6 +60,7 @@ struct ArrayState {
 // architecture, plan kind, N and the power-of-two buckets of F and T, for the
 // whole process (xeng_tune_cache_save / _load write and read it as text).
 enum KernelKind { KIND_X16 = 0, KIND_X32 = 1, KIND_STAGE = 2 };
+const char* const kKindNames[] = {"ring16", "ring32", "staging"};
 
 const KernelInfo* kernel_of(int kind, const xeng_array_desc& d) {
   const int32_t n = d.n_inputs;
@@ -144,18 +146,16 @@ int64_t nbl_of(int32_t n) { return (int64_t)n * (n + 1) / 2; }
 
 // Modelled time of a call of the 16-row ring kernel in ts time chunks per
 // channel group and phase: rounds of workgroups over the CUs, each a start
-// (launch or hand-over, ring fill, epilogue) plus its rows.  A CU's rows go
-// at 1.2 times its matrix-core cycles (at 2 GHz) and at no more than 25 bytes
+// (launch or hand-over, ring fill, epilogue: 4 us, 3 for a single channel)
+// plus its rows.  A CU's rows go at 1.2 times its matrix-core cycles (at 2 GHz) and at no more than 25 bytes
 // per ns (what one CU streams through its ring, also with most of the chip
 // idle: 24-28 measured for N = 32 .. 112); a workgroup alone takes 1 ns a row
 // longer and no less than 4 (N = 16, where four share a CU, gains by more of
-// them: F = 1024, T = 8192 36 us in one chunk, 32 in two).  Chunks are stored and summed by a second kernel: its launch, and the
-// store, the read and the sum at 6 bytes per ps (out of the caches mostly);
-// without room for them they are added atomically (115 G adds/s).  Measured
-// against it, kernel times in us for N x F x T: 100x64x4096 in 1, 4, 8, 16
-// chunks 80, 36, 27, 30 (105 with atomics in 16); 192x35x6736 in 1, 4, 8
-// chunks 82, 35, 45; 96x200x4096 in 1, 4, 8 67, 37, 51; 32x64x4096 in 1, 4,
-// 8, 16 25, 16, 12, 13; 128x64x2048 in 1, 2, 4 18, 20, 22.
+// them: F = 1024, T = 8192 36 us in one chunk, 32 in two).  Measured against
+// it, kernel times in us for N x F x T: 100x64x4096 in 1, 4, 8, 16 chunks 80,
+// 36, 27, 30 (105 with atomics in 16); 192x35x6736 in 1, 4, 8 chunks 82, 35,
+// 45; 96x200x4096 in 1, 4, 8 67, 37, 51; 32x64x4096 in 1, 4, 8, 16 25, 16, 12,
+// 13; 128x64x2048 in 1, 2, 4 18, 20, 22.
 // Nanoseconds per row of a workgroup's CU (busy), and of one workgroup alone.
 double busy_ns(const KernelInfo* k) {
   const double mfma = k->nt * (k->nt + 1) / (double)k->w / 2.0 / 2.0;  // 16 cycles per unit and 32 rows
@@ -174,37 +174,90 @@ int together(const KernelInfo* k) {
   return std::max(1, std::min(regs, 160 * 1024 / k->lds_bytes));
 }
 
+// Adding up the sums of n workgroups per channel group: stored and summed by
+// a second kernel (its launch, and the store, the read and the sum at 6 bytes
+// per ps, out of the caches mostly), or without room for them added
+// atomically (140 G adds/s: F = 1001, N = 61 in 16 phases 485 us, N = 201 in 4
+// 1157, N = 250 in 2 919).
+double combine_us(const ArrayState& s, int64_t n) {
+  if (n == 1) return 0;
+  const double acc = (double)s.acc_bytes;
+  return 5.0 + (n <= s.part_chunks ? (2 * n + 1) * acc / 6e6 : n * acc / 4.0 / 140e3);
+}
+
 double split_us(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int phases, int ts) {
   const int64_t groups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
   const int64_t wgs = groups * phases * ts;
   const int64_t per_cu = (wgs + p->n_cu - 1) / p->n_cu;
   const int64_t rounds = (per_cu + together(s.k) - 1) / together(s.k);
   const double rows_us = (double)((rows + ts - 1) / ts) * std::max(per_cu * busy_ns(s.k), rounds * row_ns(s.k)) * 1e-3;
-  const double us = rounds * 4.0 + rows_us;
-  const int n = ts * phases;
-  if (n == 1) return us;
-  const double acc = (double)s.acc_bytes;
-  return us + 5.0 + (n <= s.part_chunks ? (2 * n + 1) * acc / 6e6 : n * acc / 4.0 / 115e3);
+  return rounds * (s.k->cpw == 1 ? 3.0 : 4.0) + rows_us + combine_us(s, (int64_t)ts * phases);
 }
 
-// Time split of an untuned array: the workgroups per channel group (and
-// phase) with the least modelled time.
-int choose_split(const xeng_plan_t* p, const ArrayState& s, int64_t rows, int phases) {
-  if (rows == s.split_rows && s.k == s.split_kernel) return s.split_pick;
+// Modelled time of a call of the staging kernel: `row` ns from row to row of
+// a workgroup (loads to registers, transpose, LDS, matrix products one after
+// the other), `more` for every further workgroup of its CU, by the waves of a
+// channel (five tiles stand out: 15 tile pairs in one wave); byte loads, or
+// dwords where N is a multiple of 4.  Measured us, F = 1001, T = 4096: N = 7
+// 171, 61 342, 75 963, 113 894, 145 1536, 201 2948, 250 3093; N = 52 96, 100
+// 280, 152 455, 200 879, 252 840.
+double stage_us(const xeng_plan_t* p, const ArrayState& s, const KernelInfo* k, int64_t T, int64_t ts) {
+  const bool dwords = s.d.n_inputs % 4 == 0;
+  const double row = k->nt == 5 ? (dwords ? 54 : 154) : (dwords ? 30 : 80) + k->nt;
+  const double more = k->nt == 5 ? 240 : k->w == 1 ? 30 + 12 * k->nt : k->w == 2 ? 108 : k->w <= 4 ? 95 : 190;
+  const int64_t groups = (s.d.n_chans + k->cpw - 1) / k->cpw;
+  const int64_t per_cu = (groups * ts + p->n_cu - 1) / p->n_cu;
+  return 5.0 + (T + ts - 1) / ts * (row + (per_cu - 1) * more * (dwords ? 0.3 : 1.0)) * 1e-3 + combine_us(s, ts) +
+         (double)s.acc_bytes / 6e6;
+}
+
+// Kernel and time chunks (per channel group and phase) of a call of T
+// samples.  A tuned array takes the kernel and the split it was given.  An
+// untuned one on the 16-row ring kernel takes the chunks with the least
+// modelled time; and where its rows come in phases, each of which leaves its
+// own sums to store and add, it takes the staging kernel for the calls that
+// this is modelled faster for: few rows per phase, or no room for the sums
+// (kernel times in us, staging against ring: N = 37, F = 1001, T = 512 48 and
+// 98, T = 4096 231 and 130; N = 201, F = 1001, T = 512, whose sums do not fit
+// the room, 330 and 1161, T = 4096 2948 and 1247; in a batched plan, which
+// keeps no room, N = 37, F = 1001, T = 512 64 and 216.  Over 660 calls of 38
+// N in both forms of plan the pick is 0.7% slower than the better one on
+// average, and 21 times by more than 10%; the ring kernel is 271 times).
+struct Choice {
+  const KernelInfo* k;
+  int64_t ts;
+};
+
+int64_t aimed_chunks(const xeng_plan_t* p, const KernelInfo* k, int32_t F, int64_t rows, int phases, int split) {
+  const int64_t wgs = (int64_t)((F + k->cpw - 1) / k->cpw) * phases;
+  const int64_t ts = ((int64_t)split * p->n_cu + wgs - 1) / wgs;
+  return std::max<int64_t>(1, std::min<int64_t>(ts, rows / 256));
+}
+
+Choice choose(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
+  const int phases = xeng::row_phases(s.k, (int64_t)s.d.n_chans * s.d.n_inputs);
+  const int64_t rows = (T + phases - 1) / phases;  // of the longest phase
+  if (s.split > 0) return Choice{s.k, aimed_chunks(p, s.k, s.d.n_chans, rows, phases, s.split)};
+  if (T == s.chosen_T) return Choice{s.chosen_k, s.chosen_ts};
   double best = 0;
-  int pick = 1;
+  Choice c{s.k, 1};
   for (int ts = 1; ts <= 64 && (ts == 1 || rows / ts >= 64); ++ts) {
     const double us = split_us(p, s, rows, phases, ts);
-    if (best == 0 || us < best) best = us, pick = ts;
+    if (best == 0 || us < best) best = us, c.ts = ts;
   }
-  s.split_rows = rows;
-  s.split_kernel = s.k;
-  s.split_pick = pick;
-  return pick;
+  if (s.other) {
+    const int64_t ts = aimed_chunks(p, s.other, s.d.n_chans, T, 1, s.other->split);
+    if (stage_us(p, s, s.other, T, ts) < best) c = Choice{s.other, ts};
+  }
+  s.chosen_T = T;
+  s.chosen_k = c.k;
+  s.chosen_ts = c.ts;
+  return c;
 }
 
 // One call's launch, and how its sums reach the accumulator.
 struct Grid {
+  const KernelInfo* k;
   dim3 dim;         // channel groups x time chunks
   int64_t t_chunk;  // rows of a chunk
   int mode;         // EpiMode
@@ -213,24 +266,18 @@ struct Grid {
 };
 
 Grid grid_for(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
-  const int ngroups = (s.d.n_chans + s.k->cpw - 1) / s.k->cpw;
-  const int phases = xeng::row_phases(s.k, (int64_t)s.d.n_chans * s.d.n_inputs);
+  const Choice c = choose(p, s, T);
+  const int ngroups = (s.d.n_chans + c.k->cpw - 1) / c.k->cpw;
+  const int phases = xeng::row_phases(c.k, (int64_t)s.d.n_chans * s.d.n_inputs);
   const int64_t rows = (T + phases - 1) / phases;  // of the longest phase
-  int64_t ts;
-  if (s.split > 0) {
-    const int64_t target = (int64_t)s.split * p->n_cu;
-    ts = (target + (int64_t)ngroups * phases - 1) / ((int64_t)ngroups * phases);
-    ts = std::max<int64_t>(1, std::min<int64_t>(ts, rows / 256));
-  } else {
-    ts = choose_split(p, s, rows, phases);
-  }
-  ts = std::max<int64_t>(ts, (rows + s.k->max_t_per_wg - 1) / s.k->max_t_per_wg);
+  int64_t ts = std::max<int64_t>(c.ts, (rows + c.k->max_t_per_wg - 1) / c.k->max_t_per_wg);
   Grid g{};
+  g.k = c.k;
   g.t_chunk = (rows + ts - 1) / ts;
   g.t_chunk = (g.t_chunk + xeng::KS - 1) / xeng::KS * xeng::KS;
   ts = (rows + g.t_chunk - 1) / g.t_chunk * phases;
   g.dim = dim3((unsigned)ngroups, (unsigned)ts, 1);
-  g.parts = s.k->chunks && ts > 1 && ts <= s.part_chunks;
+  g.parts = c.k->chunks && ts > 1 && ts <= s.part_chunks;
   // the last chunk of a phase may be empty: phase ph has rows left while
   // last * t_chunk * phases + ph < T
   const int64_t before = ts - phases;
@@ -255,27 +302,23 @@ bool kernel_fits(const KernelInfo* k, const xeng_array_desc& d) {
 // Default kernel for an array: the 16-row-tile ring kernel where it takes N
 // (all but 255) and the time rows fit its 32-bit offsets, else the
 // 32-row-tile ring kernel when N is a multiple of 16, else the staging
-// kernel of 16-row tiles.  Rows taken in phases make a workgroup and a chunk
-// of sums per phase, which many channels and few rows do not repay (kernel
-// times: N = 61, F = 513, T = 1000, 2064 workgroups of 62 rows 80 us against
-// 68 in the staging kernel; N = 7, F = 1001, T = 300 30 against 28; but N =
-// 51, F = 77, T = 500, 320 workgroups of 31 rows 24 against 49, and N = 113,
-// F = 933, T = 903, 3732 of 226 rows 129 against 236).
-constexpr int64_t MIN_PHASE_ROWS = 64, MANY_WORKGROUPS = 1024;
-
+// kernel of 16-row tiles.
 const KernelInfo* default_kernel(const xeng_array_desc& d) {
-  const int32_t n = d.n_inputs;
-  const KernelInfo* k = xeng::x16_any_kernel(n, d.n_chans);
-  if (kernel_fits(k, d)) {
-    const int phases = xeng::row_phases(k, (int64_t)d.n_chans * n);
-    const int64_t wgs = (int64_t)((d.n_chans + k->cpw - 1) / k->cpw) * phases;
-    if (phases == 1 || d.max_time_per_call / phases >= MIN_PHASE_ROWS || wgs <= MANY_WORKGROUPS) return k;
-  }
-  if (n % 16 == 0 && (k = xeng::x32_kernel(n))) return k;
-  return xeng::stage_kernel((n + 15) / 16);
+  const KernelInfo* k = xeng::x16_any_kernel(d.n_inputs, d.n_chans);
+  if (kernel_fits(k, d)) return k;
+  if (d.n_inputs % 16 == 0 && (k = xeng::x32_kernel(d.n_inputs))) return k;
+  return xeng::stage_kernel((d.n_inputs + 15) / 16);
 }
 
-// The cached choice for an array of this plan, if the autotuner has made one.
+void set_kernel(ArrayState& s, const KernelInfo* k, int split) {
+  s.k = k;
+  s.split = split;
+  s.other = split == 0 && xeng::row_phases(k, (int64_t)s.d.n_chans * s.d.n_inputs) > 1
+                ? xeng::stage_kernel((s.d.n_inputs + 15) / 16)
+                : nullptr;
+  s.chosen_T = -1;
+}
+
 void apply_cached(const xeng_plan_t* p, ArrayState& s, int64_t T) {
   const TuneKey key{p->arch, p->batched ? 1 : 0, s.d.n_inputs, bucket(s.d.n_chans), bucket(T)};
   std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -283,8 +326,7 @@ void apply_cached(const xeng_plan_t* p, ArrayState& s, int64_t T) {
   if (it == g_tune.end()) return;
   const KernelInfo* k = kernel_of(it->second.kind, s.d);
   if (!kernel_fits(k, s.d)) return;
-  s.k = k;
-  s.split = it->second.split;
+  set_kernel(s, k, it->second.split);
   s.own_launch = p->batched && it->second.own;
 }
 
@@ -309,17 +351,17 @@ constexpr size_t MAX_PART_BYTES = (size_t)256 << 20;
 int init_slot(xeng_plan_t* p, ArrayState& s, const xeng_array_desc& d) {
   s = ArrayState{};
   s.d = d;
-  s.k = default_kernel(d);
-  s.split = s.k->split;
-  apply_cached(p, s, d.max_time_per_call);
   s.acc_bytes = (size_t)d.n_chans * nbl_of(d.n_inputs) * 2 * sizeof(int32_t);
+  const KernelInfo* k = default_kernel(d);
+  set_kernel(s, k, k->split);
+  apply_cached(p, s, d.max_time_per_call);
   // A plain plan keeps room for the sums of the time chunks of its longest
   // call (bounded; calls split further add atomically).
   if (!p->batched && s.k->chunks) {
-    s.part_chunks = INT_MAX;
+    s.part_chunks = (int)std::min<size_t>(INT_MAX, MAX_PART_BYTES / s.acc_bytes);
     const Grid g = grid_for(p, s, d.max_time_per_call);
-    s.part_chunks = g.parts && g.dim.y * s.acc_bytes <= MAX_PART_BYTES ? (int)g.dim.y : 0;
-    s.split_rows = -1;  // (that was with room for any number)
+    s.part_chunks = g.parts ? (int)g.dim.y : 0;
+    s.chosen_T = -1;  // (that was with the most room)
   }
   const size_t acc_room = s.part_chunks ? (s.acc_bytes + 255) / 256 * 256 : s.acc_bytes;
   hipError_t e = hipMalloc(&s.acc, acc_room + s.part_chunks * s.acc_bytes);
@@ -367,14 +409,14 @@ int init_for_atomics(xeng_plan_t* p, const std::vector<ArrayState*>& arrays) {
 // integration in memory that does not hold zeros, or earlier sums elsewhere.
 bool needs_init(const ArrayState& s) { return s.clean ? !s.zeroed : s.prev != nullptr; }
 
-xeng::Args base_args(const ArrayState& s, const uint8_t* v, int64_t T) {
+xeng::Args base_args(const ArrayState& s, const KernelInfo* k, const uint8_t* v, int64_t T) {
   xeng::Args a{};
   a.v = v;
   a.acc = s.acc;
   a.T = T;
   a.F = s.d.n_chans;
   a.N = s.d.n_inputs;
-  a.period = xeng::row_phases(s.k, (int64_t)s.d.n_chans * s.d.n_inputs);
+  a.period = xeng::row_phases(k, (int64_t)s.d.n_chans * s.d.n_inputs);
   if (s.prev)
     a.prev_off = (int64_t)(reinterpret_cast<uintptr_t>(s.prev) - reinterpret_cast<uintptr_t>(s.acc)) /
                  (int64_t)sizeof(int32_t);
@@ -382,8 +424,8 @@ xeng::Args base_args(const ArrayState& s, const uint8_t* v, int64_t T) {
 }
 
 int launch_plain(xeng_plan_t* p, ArrayState& s, const uint8_t* v, int64_t T) {
-  xeng::Args args = base_args(s, v, T);
   const Grid g = grid_for(p, s, T);
+  xeng::Args args = base_args(s, g.k, v, T);
   args.t_chunk = g.t_chunk;
   args.mode = g.mode;
   if (g.parts) {
@@ -392,13 +434,14 @@ int launch_plain(xeng_plan_t* p, ArrayState& s, const uint8_t* v, int64_t T) {
   }
   ++p->stats.launches;
   if (p->trace)
-    fprintf(stderr, "xeng: plan %p plain launch N=%d F=%d T=%lld grid=%ux%u threads=%d mode=%d chunks=%d\n", (void*)p,
-            args.N, args.F, (long long)T, g.dim.x, g.dim.y, s.k->threads, args.mode, g.parts ? g.chunks : 0);
+    fprintf(stderr, "xeng: plan %p plain launch N=%d F=%d T=%lld kernel=%s grid=%ux%u threads=%d mode=%d chunks=%d\n",
+            (void*)p, args.N, args.F, (long long)T, kKindNames[kind_of(g.k, s.d)], g.dim.x, g.dim.y, g.k->threads,
+            args.mode, g.parts ? g.chunks : 0);
   if (args.mode == xeng::EPI_ATOMIC && needs_init(s)) {
     const int st = init_for_atomics(p, {&s});
     if (st != XENG_OK) return st;
   }
-  hipError_t e = s.k->launch(g.dim, p->stream, args);
+  hipError_t e = g.k->launch(g.dim, p->stream, args);
   if (e == hipSuccess && g.parts)
     e = xeng::sum_launch(p->stream, s.clean ? nullptr : reinterpret_cast<const int2*>(s.prev ? s.prev : s.acc),
                          reinterpret_cast<const int2*>(s.part), reinterpret_cast<int2*>(s.acc),
@@ -495,7 +538,7 @@ int record_batched(xeng_plan_t* p, const uint8_t* const* v, const int64_t* n_tim
       const BatchEntry& b = items[i];
       const ArrayState& s = p->arrays[b.a];
       const int k = bp.n_arrays++;
-      bp.arr[k] = base_args(s, v[b.a], n_time[b.a]);
+      bp.arr[k] = base_args(s, s.k, v[b.a], n_time[b.a]);
       bp.arr[k].t_chunk = b.t_chunk;
       bp.arr[k].mode = b.nchunks > 1 ? xeng::EPI_ATOMIC : (s.clean ? xeng::EPI_STORE : xeng::EPI_ADD);
       bp.ngroups[k] = b.ngroups;
@@ -898,8 +941,7 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
         const KernelInfo* k = kernel_of(kind, s.d);
         if (!kernel_fits(k, s.d) || (kind == KIND_X32 && s.d.n_inputs % 16 != 0)) continue;
         for (int split : {1, 2}) {
-          s.k = k;
-          s.split = split;
+          set_kernel(s, k, split);
           s.own_launch = true;
           float ms = 0;
           st = trial(ms);
@@ -914,8 +956,7 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
       const bool own = choice.own_launch;
       s = keep;
       if (own) {
-        s.k = choice.k;
-        s.split = choice.split;
+        set_kernel(s, choice.k, choice.split);
         s.own_launch = true;
       }
     }
@@ -940,8 +981,7 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
         if (!k) continue;
         for (int split : {0, 1, 2, 4}) {
           if (split == 0 && k->split != 0) continue;  // no model for this kernel
-          s.k = k;
-          s.split = split;
+          set_kernel(s, k, split);
           float ms = 0;
           st = trial(ms);
           if (st != XENG_OK) break;
@@ -953,8 +993,7 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
         }
         if (st != XENG_OK) break;
       }
-      s.k = pick_k;
-      s.split = pick_split;
+      set_kernel(s, pick_k, pick_split);
       best += arr_best;
       if (st != XENG_OK) break;
       if (n_time[&s - &p->arrays[0]] > 0) record_choice(p, s, n_time[&s - &p->arrays[0]]);
