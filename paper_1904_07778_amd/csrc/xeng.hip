@@ -1035,7 +1035,7 @@ int xeng_tune_cache_load(const char* path) {
     int b, n, fb, tb, kind, split, own;
     if (sscanf(line, "%127s %d %d %d %d %d %d %d", arch, &b, &n, &fb, &tb, &kind, &split, &own) != 8 ||
         n < 0 || n > XENG_MAX_INPUTS || (n == 0 && !b) || kind < KIND_X16 || kind > KIND_STAGE ||
-        split < (b || kind != KIND_X16 ? 1 : 0) || split > 64) {
+        split < (kind != KIND_X16 ? 1 : 0) || split > 64) {  // 0: modelled, on the ring kernel and in a batch
       st = XENG_EINVAL;  // malformed line: skipped, reported
       continue;
     }
