@@ -235,7 +235,9 @@ int xeng_autotune(xeng_plan_t *p, const uint8_t *const *d_voltages, const int64_
  * xeng_tune_cache_save / xeng_tune_cache_load / xeng_tune_cache_clear - the
  * process-wide tuning cache of xeng_autotune as a text file (one choice per
  * line: architecture, batched, N, log2 F bucket, log2 T bucket, tile shape,
- * time split, own launch; a batched plan's items per workgroup are kept as a
+ * time split, own launch, and last, where it is not 1, the number of phases
+ * that the ring kernel takes the rows in when N x F is no multiple of its load
+ * unit; a batched plan's items per workgroup are kept as a
  * line with N = 0, F bucket 0 and the log2 bucket of its array count in
  * place of the T bucket), so a later process skips the timing.  Loading
  * adds to (and overrides) what the cache holds; plans made afterwards use

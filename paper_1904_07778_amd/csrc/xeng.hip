@@ -87,8 +87,9 @@ int bucket(int64_t v) {  // ceil(log2 v)
 struct TuneKey {
   std::string arch;
   int batched, n, fb, tb;
+  int phases;  // of the 16-row ring kernel (row_phases): they depend on F itself
   bool operator<(const TuneKey& o) const {
-    return std::tie(arch, batched, n, fb, tb) < std::tie(o.arch, o.batched, o.n, o.fb, o.tb);
+    return std::tie(arch, batched, n, fb, tb, phases) < std::tie(o.arch, o.batched, o.n, o.fb, o.tb, o.phases);
   }
 };
 struct TuneVal {
@@ -319,10 +320,23 @@ void set_kernel(ArrayState& s, const KernelInfo* k, int split) {
   s.chosen_T = -1;
 }
 
+TuneKey tune_key(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
+  const KernelInfo* k = kernel_of(KIND_X16, s.d);
+  return TuneKey{p->arch, p->batched ? 1 : 0, s.d.n_inputs, bucket(s.d.n_chans), bucket(T),
+                 k ? xeng::row_phases(k, (int64_t)s.d.n_chans * s.d.n_inputs) : 1};
+}
+
 void apply_cached(const xeng_plan_t* p, ArrayState& s, int64_t T) {
-  const TuneKey key{p->arch, p->batched ? 1 : 0, s.d.n_inputs, bucket(s.d.n_chans), bucket(T)};
+  TuneKey key = tune_key(p, s, T);
   std::lock_guard<std::mutex> lock(g_tune_mu);
   auto it = g_tune.find(key);
+  if (it == g_tune.end() && key.phases > 1) {
+    // A choice made for rows of whole load units (and all lines of older
+    // files) says nothing of the ring kernel in phases.
+    key.phases = 1;
+    it = g_tune.find(key);
+    if (it != g_tune.end() && it->second.kind == KIND_X16) return;
+  }
   if (it == g_tune.end()) return;
   const KernelInfo* k = kernel_of(it->second.kind, s.d);
   if (!kernel_fits(k, s.d)) return;
@@ -332,7 +346,7 @@ void apply_cached(const xeng_plan_t* p, ArrayState& s, int64_t T) {
 
 // The batched plan's own choice (items per workgroup) is kept under N = 0,
 // keyed by the base-2 bucket of the plan's array count.
-TuneKey plan_key(const xeng_plan_t* p, int32_t n_arrays) { return TuneKey{p->arch, 1, 0, 0, bucket(n_arrays)}; }
+TuneKey plan_key(const xeng_plan_t* p, int32_t n_arrays) { return TuneKey{p->arch, 1, 0, 0, bucket(n_arrays), 1}; }
 
 void apply_cached_plan(xeng_plan_t* p, int32_t n_arrays) {
   std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -341,7 +355,7 @@ void apply_cached_plan(xeng_plan_t* p, int32_t n_arrays) {
 }
 
 void record_choice(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
-  const TuneKey key{p->arch, p->batched ? 1 : 0, s.d.n_inputs, bucket(s.d.n_chans), bucket(T)};
+  const TuneKey key = tune_key(p, s, T);
   std::lock_guard<std::mutex> lock(g_tune_mu);
   g_tune[key] = TuneVal{kind_of(s.k, s.d), s.split, s.own_launch ? 1 : 0};
 }
@@ -1016,8 +1030,9 @@ int xeng_tune_cache_save(const char* path) {
   {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     for (const auto& kv : g_tune)
-      fprintf(f, "%s %d %d %d %d %d %d %d\n", kv.first.arch.c_str(), kv.first.batched, kv.first.n, kv.first.fb,
-              kv.first.tb, kv.second.kind, kv.second.split, kv.second.own);
+      fprintf(f, kv.first.phases > 1 ? "%s %d %d %d %d %d %d %d %d\n" : "%s %d %d %d %d %d %d %d\n",
+              kv.first.arch.c_str(), kv.first.batched, kv.first.n, kv.first.fb, kv.first.tb, kv.second.kind,
+              kv.second.split, kv.second.own, kv.first.phases);
   }
   return fclose(f) == 0 ? XENG_OK : XENG_EINVAL;
 }
@@ -1032,14 +1047,14 @@ int xeng_tune_cache_load(const char* path) {
   while (fgets(line, sizeof line, f)) {
     if (line[0] == '#' || line[0] == '\n') continue;
     char arch[128];
-    int b, n, fb, tb, kind, split, own;
-    if (sscanf(line, "%127s %d %d %d %d %d %d %d", arch, &b, &n, &fb, &tb, &kind, &split, &own) != 8 ||
+    int b, n, fb, tb, kind, split, own, phases = 1;
+    if (sscanf(line, "%127s %d %d %d %d %d %d %d %d", arch, &b, &n, &fb, &tb, &kind, &split, &own, &phases) < 8 ||
         n < 0 || n > XENG_MAX_INPUTS || (n == 0 && !b) || kind < KIND_X16 || kind > KIND_STAGE ||
-        split < (kind != KIND_X16 ? 1 : 0) || split > 64) {  // 0: modelled, on the ring kernel and in a batch
+        split < (kind != KIND_X16 ? 1 : 0) || split > 64 || phases < 1) {  // 0: modelled, on the ring kernel and in a batch
       st = XENG_EINVAL;  // malformed line: skipped, reported
       continue;
     }
-    g_tune[TuneKey{arch, b ? 1 : 0, n, fb, tb}] = TuneVal{kind, split, own ? 1 : 0};
+    g_tune[TuneKey{arch, b ? 1 : 0, n, fb, tb, phases}] = TuneVal{kind, split, own ? 1 : 0};
   }
   fclose(f);
   return st;

@@ -22,3 +22,25 @@ def test_a_tuned_batch_is_saved_and_loaded(tmp_path):
     assert out == ["ok"]
     saved = open(path).read()
     assert saved == open(path + "2").read() and saved.count("gfx950 1 ") == 4
+
+
+def test_a_choice_for_whole_rows_is_not_one_for_rows_in_phases(tmp_path):
+    """F = 1024 and F = 999 share a bucket; N = 99 takes the rows of the first
+    whole, those of the second in 16 phases."""
+    path = tmp_path / "cache.txt"
+    path.write_text("gfx950 0 99 10 8 0 1 0\n")
+    _, trace = run(f"""
+        X.xeng_tune_cache_load({str(path)!r})
+        for f in (1024, 999): call(X.xeng_plan([(99, f, 256)]), [256])
+    """)
+    assert ["kernel=ring16" in l for l in trace] == [True, False], trace
+    # a staging choice is one for any rows; a choice for phases is kept as one
+    path.write_text("gfx950 0 99 10 8 2 1 0\ngfx950 0 51 7 9 0 1 0 16\n")
+    out, trace = run(f"""
+        X.xeng_tune_cache_load({str(path)!r})
+        for f in (1024, 999): call(X.xeng_plan([(99, f, 256)]), [256])
+        for f in (77, 112): call(X.xeng_plan([(51, f, 500)]), [500])
+        X.xeng_tune_cache_save({str(path)!r})
+    """)
+    assert ["kernel=ring16" in l for l in trace] == [False, False, True, True], trace
+    assert "grid=20x16" in trace[2] and "gfx950 0 51 7 9 0 1 0 16\n" in path.read_text()
