@@ -91,7 +91,7 @@ enum {
  * The array indices of later calls are slots 0 .. n_arrays-1 (see
  * xeng_attach for more).  Allocates the HBM-resident int32 accumulators
  * (zeroed); a plain plan whose calls are split along time keeps room for the
- * chunks' sums with them, up to 256 MB.  Errors: EINVAL (null out, null arrays with n_arrays > 0, N or F
+ * chunks' sums beside them, up to 256 MB where that can be had.  Errors: EINVAL (null out, null arrays with n_arrays > 0, N or F
  * or max_time_per_call out of range, unknown flags), ENOMEM, EDEVICE.
  */
 int xeng_plan(xeng_plan_t **out, const xeng_array_desc *arrays, int32_t n_arrays,

@@ -47,8 +47,8 @@ struct ArrayState {
   const KernelInfo* k = nullptr;  // kernel of the plain launch
   int split = 0;                  // plain launch: aim for split * n_cu workgroups; 0: modelled (choose)
   const KernelInfo* other = nullptr;  // the kernel of the calls it is modelled faster for (choose)
-  int32_t* part = nullptr;        // plain plan: room for part_chunks time chunks' sums, in
-  int part_chunks = 0;            // the accumulator's allocation
+  int32_t* part = nullptr;        // plain plan: room for part_chunks time chunks' sums
+  int part_chunks = 0;
   mutable int64_t chosen_T = -1;  // choose's last pick, of calls of this length
   mutable const KernelInfo* chosen_k = nullptr;
   mutable int64_t chosen_ts = 0;
@@ -362,6 +362,18 @@ void record_choice(const xeng_plan_t* p, const ArrayState& s, int64_t T) {
 
 constexpr size_t MAX_PART_BYTES = (size_t)256 << 20;
 
+// Chunks of the longest call that a plain plan keeps room for (bounded; calls
+// split further add atomically).
+int room_chunks(const xeng_plan_t* p, ArrayState& s) {
+  if (p->batched || !s.k->chunks) return 0;
+  const int keep = s.part_chunks;
+  s.part_chunks = (int)std::min<size_t>(INT_MAX, MAX_PART_BYTES / s.acc_bytes);
+  const Grid g = grid_for(p, s, s.d.max_time_per_call);
+  s.part_chunks = keep;
+  s.chosen_T = -1;  // (that was with the most room)
+  return g.parts ? (int)g.dim.y : 0;
+}
+
 int init_slot(xeng_plan_t* p, ArrayState& s, const xeng_array_desc& d) {
   s = ArrayState{};
   s.d = d;
@@ -369,22 +381,20 @@ int init_slot(xeng_plan_t* p, ArrayState& s, const xeng_array_desc& d) {
   const KernelInfo* k = default_kernel(d);
   set_kernel(s, k, k->split);
   apply_cached(p, s, d.max_time_per_call);
-  // A plain plan keeps room for the sums of the time chunks of its longest
-  // call (bounded; calls split further add atomically).
-  if (!p->batched && s.k->chunks) {
-    s.part_chunks = (int)std::min<size_t>(INT_MAX, MAX_PART_BYTES / s.acc_bytes);
-    const Grid g = grid_for(p, s, d.max_time_per_call);
-    s.part_chunks = g.parts ? (int)g.dim.y : 0;
-    s.chosen_T = -1;  // (that was with the most room)
-  }
-  const size_t acc_room = s.part_chunks ? (s.acc_bytes + 255) / 256 * 256 : s.acc_bytes;
-  hipError_t e = hipMalloc(&s.acc, acc_room + s.part_chunks * s.acc_bytes);
+  hipError_t e = hipMalloc(&s.acc, s.acc_bytes);
   if (e != hipSuccess) {
     s.acc = nullptr;
     return e == hipErrorOutOfMemory ? fail(p, XENG_ENOMEM, "accumulator of %zu bytes", s.acc_bytes)
                                     : hip_fail(p, e, "accumulator allocation");
   }
-  if (s.part_chunks) s.part = s.acc + acc_room / sizeof(int32_t);
+  // The room is not needed: where there is no memory for it, split calls add
+  // atomically.
+  s.part_chunks = room_chunks(p, s);
+  if (s.part_chunks && hipMalloc(&s.part, s.part_chunks * s.acc_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    s.part = nullptr;
+    s.part_chunks = 0;
+  }
   e = hipMemsetAsync(s.acc, 0, s.acc_bytes, p->stream);
   if (e != hipSuccess) return hip_fail(p, e, "accumulator clear");
   s.active = true;
@@ -1164,8 +1174,10 @@ void xeng_destroy(xeng_plan_t* p) {
     if (p->exec[i]) (void)hipGraphExecDestroy(p->exec[i]);
     if (p->done[i]) (void)hipEventDestroy(p->done[i]);
   }
-  for (ArrayState& s : p->arrays)
+  for (ArrayState& s : p->arrays) {
     if (s.acc) (void)hipFree(s.acc);
+    if (s.part) (void)hipFree(s.part);
+  }
   if (p->counters) (void)hipFree(p->counters);
   if (p->own_stream && p->stream) (void)hipStreamDestroy(p->stream);
   delete p;

@@ -69,3 +69,23 @@ def test_shapes_of_the_gpu_tests_take_the_paths_they_name():
     """)
     assert launches(trace) == [((37, 301, 100), "staging", 0), ((37, 301, 4096), "ring16", 0),
                                ((251, 5, 3000), "ring16", ATOMIC), ((53, 3, 3000), "ring16", ATOMIC)]
+
+
+def test_a_plan_is_made_where_the_accumulator_alone_fits():
+    """The room for time chunks' sums is left out when there is no memory for
+    it (the call adds atomically then); nothing stays allocated."""
+    out, trace = run("""
+        d = (100, 64, 4096)
+        acc = X.xeng_accumulator_bytes(100, 64)
+        for limit in (1 << 40, 2 * acc, acc, acc - 1):
+            stub.stub_limit(limit)
+            try:
+                h = X.xeng_plan([d])
+            except X.XengError as e:
+                print(limit < acc, e.status == X.XENG_ENOMEM)
+            else:
+                call(h, [4096]); print(stub.stub_used() // acc); X.xeng_destroy(h)
+        print(stub.stub_used())
+    """)
+    assert out[1:] == ["1", "1", "True True", "0"] and int(out[0]) > 2
+    assert [m for _, _, m in launches(trace)] == [0, ATOMIC, ATOMIC]
