@@ -47,8 +47,10 @@ struct ArrayState {
   const KernelInfo* k = nullptr;  // kernel of the plain launch
   int split = 0;                  // plain launch: aim for split * n_cu workgroups; 0: modelled (choose)
   const KernelInfo* other = nullptr;  // the kernel of the calls it is modelled faster for (choose)
-  int32_t* part = nullptr;        // plain plan: room for part_chunks time chunks' sums
-  int part_chunks = 0;
+  int32_t* part = nullptr;        // plain plan: room for time chunks' sums, of which a call
+  int part_chunks = 0;            // uses part_chunks; allocated for part_room
+  int part_room = 0;
+  int32_t* old_part = nullptr;    // the room before the autotuner chose a larger one
   mutable int64_t chosen_T = -1;  // choose's last pick, of calls of this length
   mutable const KernelInfo* chosen_k = nullptr;
   mutable int64_t chosen_ts = 0;
@@ -395,6 +397,7 @@ int init_slot(xeng_plan_t* p, ArrayState& s, const xeng_array_desc& d) {
     s.part = nullptr;
     s.part_chunks = 0;
   }
+  s.part_room = s.part_chunks;
   e = hipMemsetAsync(s.acc, 0, s.acc_bytes, p->stream);
   if (e != hipSuccess) return hip_fail(p, e, "accumulator clear");
   s.active = true;
@@ -991,33 +994,56 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
     }
   } else {
     // per array: tile shape (32-row tiles of the ring kernel or 16-row tiles
-    // of the staging kernel) and workgroups per CU of the time split
+    // of the staging kernel) and workgroups per CU of the time split, each
+    // timed with the chunk room that a new plan with that choice would have
     for (ArrayState& s : p->arrays) {
       if (!s.active) continue;
       std::vector<const KernelInfo*> kernels;
       if (kernel_fits(kernel_of(KIND_X16, s.d), s.d)) kernels.push_back(kernel_of(KIND_X16, s.d));
       if (s.d.n_inputs % 16 == 0) kernels.push_back(xeng::x32_kernel(s.d.n_inputs));
       kernels.push_back(xeng::stage_kernel((s.d.n_inputs + 15) / 16));
-      const KernelInfo* pick_k = s.k;
-      int pick_split = s.split;
-      float arr_best = 0;
-      for (const KernelInfo* k : kernels) {
-        if (!k) continue;
-        for (int split : {0, 1, 2, 4}) {
-          if (split == 0 && k->split != 0) continue;  // no model for this kernel
-          set_kernel(s, k, split);
-          float ms = 0;
-          st = trial(ms);
-          if (st != XENG_OK) break;
-          if (arr_best == 0 || ms < arr_best) {
-            arr_best = ms;
-            pick_k = k;
-            pick_split = split;
-          }
-        }
-        if (st != XENG_OK) break;
+      std::vector<std::pair<const KernelInfo*, int>> cands;
+      for (const KernelInfo* k : kernels)
+        for (int split : {0, 1, 2, 4})
+          if (k && (split != 0 || k->split == 0)) cands.emplace_back(k, split);  // (0: only where modelled)
+      const std::pair<const KernelInfo*, int> first{s.k, s.split};
+      int32_t* const own = s.part;  // kept until the plan goes: calls captured by the caller may name it
+      const int own_chunks = s.part_room;
+      int most = 0;
+      for (const auto& c : cands) {
+        set_kernel(s, c.first, c.second);
+        most = std::max(most, room_chunks(p, s));
       }
-      set_kernel(s, pick_k, pick_split);
+      int32_t* trial_room = nullptr;
+      if (most > own_chunks && hipMalloc(&trial_room, most * s.acc_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        trial_room = nullptr;
+      }
+      auto take = [&](const std::pair<const KernelInfo*, int>& c) {
+        set_kernel(s, c.first, c.second);
+        const int chunks = room_chunks(p, s);
+        s.part = chunks > own_chunks && trial_room ? trial_room : own;
+        s.part_chunks = std::min(chunks, s.part == trial_room ? most : own_chunks);
+      };
+      std::pair<const KernelInfo*, int> pick = first;
+      float arr_best = 0;
+      for (const auto& c : cands) {
+        take(c);
+        float ms = 0;
+        st = trial(ms);
+        if (st != XENG_OK) break;
+        if (arr_best == 0 || ms < arr_best) {
+          arr_best = ms;
+          pick = c;
+        }
+      }
+      take(pick);
+      if (trial_room && s.part == trial_room) {
+        s.part_room = most;
+        s.old_part = own;
+      } else if (trial_room) {
+        (void)hipFree(trial_room);
+      }
       best += arr_best;
       if (st != XENG_OK) break;
       if (n_time[&s - &p->arrays[0]] > 0) record_choice(p, s, n_time[&s - &p->arrays[0]]);
@@ -1177,6 +1203,7 @@ void xeng_destroy(xeng_plan_t* p) {
   for (ArrayState& s : p->arrays) {
     if (s.acc) (void)hipFree(s.acc);
     if (s.part) (void)hipFree(s.part);
+    if (s.old_part) (void)hipFree(s.old_part);
   }
   if (p->counters) (void)hipFree(p->counters);
   if (p->own_stream && p->stream) (void)hipStreamDestroy(p->stream);

@@ -44,3 +44,37 @@ def test_a_choice_for_whole_rows_is_not_one_for_rows_in_phases(tmp_path):
     """)
     assert ["kernel=ring16" in l for l in trace] == [False, False, True, True], trace
     assert "grid=20x16" in trace[2] and "gfx950 0 51 7 9 0 1 0 16\n" in path.read_text()
+
+
+def test_every_candidate_is_timed_with_the_room_it_would_have():
+    """A new plan of a split choice keeps room for the chunks' sums, so no
+    trial of a kernel that can store them adds atomically, whatever the plan
+    under the tuner was made with; the tuned plan frees all it holds."""
+    out, trace = run("""
+        d = (96, 1024, 4096)
+        h = X.xeng_plan([d]); before = stub.stub_used()
+        X.xeng_autotune(h, [1 << 32], [d[2]], 1)
+        print(before == X.xeng_accumulator_bytes(*d[:2]), stub.stub_used() == before)
+        X.xeng_destroy(h); print(stub.stub_used())
+    """)
+    assert out == ["True True", "0"]
+    split = [l for l in trace if "kernel=ring32" not in l and "x1 threads" not in l]
+    assert split and not [l for l in split if "mode=2" in l], split
+
+
+def test_a_choice_that_needs_more_room_keeps_it():
+    """The third candidate (ring kernel, two workgroups per CU) is the fastest."""
+    out, trace = run("""
+        d = (96, 1024, 4096)
+        h = X.xeng_plan([d]); before = stub.stub_used()
+        stub.stub_fast(2)
+        X.xeng_autotune(h, [1 << 32], [d[2]], 1)
+        print(stub.stub_used() // before)
+        stub.stub_fast(-1)
+        call(h, [d[2]])
+        new = X.xeng_plan([d]); call(new, [d[2]])
+        X.xeng_destroy(h), X.xeng_destroy(new); print(stub.stub_used())
+    """)
+    assert int(out[0]) > 1 and out[1] == "0"
+    # the tuned plan's next call and a new plan's first
+    assert all("kernel=ring16 grid=256x2 threads=256 mode=0 chunks=2" in l for l in trace[-2:]), trace[-2:]
