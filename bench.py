@@ -128,7 +128,7 @@ def tuned_choices(shapes, batched: bool) -> str:
                    f"N={n}: {KIND_NAMES.get(c[0], c[0])} split {c[1]}{' own launch' if c[2] else ''}")
     plan = table.get((1, 0, 0, _bucket(len(shapes)))) if batched else None
     if plan is not None:
-        out.append(f"batch launch: {plan[1]} items per CU")
+        out.append(f"batch launch: {plan[1]} items per CU" if plan[1] else "batch launch: modelled items")
     return "; ".join(out)
 
 

@@ -213,8 +213,9 @@ int64_t xeng_accumulator_bytes(int32_t n_inputs, int32_t n_chans);
  *   d_voltages, n_time  one call's arguments, as for xeng_correlate.
  *   reps                calls timed per candidate (>= 1).
  *   best_ms             optional out: mean time of one call with the choice.
- * Batched plan: the work-item granularity of the batch launch (about
- * 1, 2, 4 or 8 items per compute unit; items are cut along time), then per
+ * Batched plan: the work-item granularity of the batch launch (as the
+ * library models it for each call, or about 1, 2, 4 or 8 items per compute
+ * unit; items are cut along time), then per
  * array, largest first, whether it runs as items of the batch launch
  * (16-row tiles) or as a plain launch of its own inside the same graph, with
  * the tile shape and time split that suit it.  Plain plan, per array: the

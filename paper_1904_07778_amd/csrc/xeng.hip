@@ -935,16 +935,16 @@ int xeng_autotune(xeng_plan_t* p, const uint8_t* const* d_voltages, const int64_
 
   float best = 0;
   if (p->batched) {
-    // work-item granularity of the batch launch
-    const int cand[] = {1, 2, 4, 8};
+    // work-item granularity of the batch launch (0: modelled for each call)
     int pick = p->batch_split;
-    for (int i = 0; i < 4 && st == XENG_OK; ++i) {
-      p->batch_split = cand[i];
+    for (int cand : {0, 1, 2, 4, 8}) {
+      if (st != XENG_OK) break;
+      p->batch_split = cand;
       float ms = 0;
       st = trial(ms);
       if (st == XENG_OK && (best == 0 || ms < best)) {
         best = ms;
-        pick = cand[i];
+        pick = cand;
       }
     }
     p->batch_split = pick;

@@ -78,3 +78,13 @@ def test_a_choice_that_needs_more_room_keeps_it():
     assert int(out[0]) > 1 and out[1] == "0"
     # the tuned plan's next call and a new plan's first
     assert all("kernel=ring16 grid=256x2 threads=256 mode=0 chunks=2" in l for l in trace[-2:]), trace[-2:]
+
+
+def test_the_batch_tuner_tries_the_modelled_items(tmp_path):
+    """Its first candidate is what an untuned plan does (0 items per CU asked for)."""
+    path = tmp_path / "cache.txt"
+    run(f"""
+        X.xeng_autotune(X.xeng_plan([(32, 64, 2048), (96, 128, 1024)]), [1 << 32] * 2, [2048, 1024], 1)
+        X.xeng_tune_cache_save({str(path)!r})
+    """)
+    assert "gfx950 1 0 0 1 0 0 0\n" in path.read_text()
