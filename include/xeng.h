@@ -103,7 +103,9 @@ int xeng_plan(xeng_plan_t **out, const xeng_array_desc *arrays, int32_t n_arrays
  *   d_voltages  one device pointer per slot (xeng_slots), each uint8
  *               [n_time[a]][F][N], 16-byte aligned; caller-owned, must stay
  *               valid until the stream reaches this work.  May be NULL where
- *               n_time[a] == 0.
+ *               n_time[a] == 0.  (Read in whole dwords: where the block's size
+ *               is no multiple of 4, up to 3 bytes after it are read and not
+ *               used.)
  *   n_time      one sample count per slot; 0 skips that array (and must be 0
  *               for a free slot).
  * The block is added to the array's running integration.  A batched plan

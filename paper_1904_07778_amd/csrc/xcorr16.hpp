@@ -51,6 +51,7 @@
 #pragma once
 #include <type_traits>
 
+#include "ragged_rows.hpp"
 #include "xcorr.hpp"
 
 namespace xeng {
@@ -430,6 +431,7 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
   // offset of the phase's first row in its load unit; rs32 is a whole number of units
   const uint64_t phase_off = LD == LD_EXACT ? 0 : (uint64_t)phase * (uint32_t)(a.F * nin);
   const uint32_t sub = (uint32_t)phase_off & (UNIT - 1);
+  const uint32_t slack = LD == LD_EXACT ? 0 : row_slack(rs32, sub, (uint32_t)(a.F * nin));
   const int nch_valid = min(CPW, a.F - f0);             // the last group may be short of channels
 
   // ---- producer: the wave-wide 1 KB loads q = 0 .. LOADS-1 of every stage.
@@ -487,7 +489,8 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
     v4i rsrc;
     rsrc[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)b);
     rsrc[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xFFFFu));
-    rsrc[2] = __builtin_amdgcn_readfirstlane((int)((uint32_t)rows * rs32));
+    rsrc[2] = __builtin_amdgcn_readfirstlane(
+        (int)(LD == LD_EXACT ? (uint32_t)rows * rs32 : stage_bytes(rows, rs32, slack)));
     rsrc[3] = 0x00020000;  // raw buffer, 32-bit data format
     const uint32_t base = ring_base + (uint32_t)((st % S) * C::STAGE_BYTES);
     if constexpr (LD == LD_DWORD) {
