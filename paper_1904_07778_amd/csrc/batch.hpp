@@ -9,8 +9,8 @@
 // (x16::wave_main) with the launch shape compiled for its N, so the sums are
 // bit-identical to the plain engine's.
 //
-// The host launches one workgroup per item (per_wg = 1), which the hardware
-// starts as CUs become free.  With one workgroup per CU that takes items
+// The host launches one workgroup per item, which the hardware starts as CUs
+// become free.  With one workgroup per CU that takes items
 // until all are done, the next item's ring loads share the memory counter
 // with the last item's stores and wait for them, where a new workgroup starts
 // while they drain: N = 192, F = 1024, T = 1024, adding, 169 us per call in
@@ -51,7 +51,6 @@ struct Params {
   int32_t nchunks[MAX_ARRAYS];   // time chunks
   int32_t n_arrays;
   int32_t* counters;             // [QUEUES + 1], zero between launches
-  int32_t per_wg;                // items a workgroup takes at most
 };
 
 // Channel groups [begin, end) of queue x for an array with g groups.
@@ -80,7 +79,10 @@ __device__ __forceinline__ void run_if(int n, const Args& a, uint8_t* lds, int g
   }
 }
 
-// The persistent kernel (k_batch.hip) and its host-side launch.
+// Items of one launch: a grid holds fewer than 2^32 threads.
+constexpr int64_t MAX_ITEMS = (((int64_t)1 << 32) - 1) / THREADS;
+
+// The kernel (k_batch.hip) and its launch on one workgroup per item.
 hipError_t launch(int grid, hipStream_t s, const Params& p);
 const void* kernel_function();
 

@@ -13,7 +13,6 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1))) vo
   __shared__ __attribute__((aligned(1024))) uint8_t lds[lds_bytes()];
   __shared__ int item_slot;
   const int home = blockIdx.x % QUEUES;
-  int left = p.per_wg;
 
   // items of array k in queue x
   auto count = [&](int k, int x) {
@@ -21,35 +20,33 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1))) vo
     return (range_begin(g, x + 1) - range_begin(g, x)) * p.nchunks[k];
   };
 
-  for (int d = 0; d < QUEUES;) {
-    const int x = (home + d) % QUEUES;
+  // Find this workgroup's item: in the queue of its XCD, or the next that has one.
+  int k = p.n_arrays, q = 0, x = home;
+  for (int d = 0; d < QUEUES; ++d) {
+    x = (home + d) % QUEUES;
     if (threadIdx.x == 0) item_slot = atomicAdd(&p.counters[x], 1);
     __syncthreads();
-    int q = item_slot;
+    q = item_slot;
     __syncthreads();  // every wave has read the slot before it is written again
-    int k = 0;
-    for (; k < p.n_arrays; ++k) {
+    for (k = 0; k < p.n_arrays; ++k) {
       const int c = count(k, x);
       if (q < c) break;
       q -= c;
     }
-    if (k == p.n_arrays) {  // queue x is exhausted: move on to the next one
-      ++d;
-      continue;
-    }
+    if (k < p.n_arrays) break;
+  }
+  if (k < p.n_arrays) {
     k = __builtin_amdgcn_readfirstlane(k);
     q = __builtin_amdgcn_readfirstlane(q);
     const int g0 = range_begin(p.ngroups[k], x);
     const int ng = range_begin(p.ngroups[k], x + 1) - g0;
     const Args a = p.arr[k];
-    // An opaque copy of the thread index per item: everything the item body
-    // derives from it stays inside the loop, instead of being hoisted out for
-    // all twelve launch shapes at once (which would not fit the registers).
+    // An opaque copy of the thread index: what the item bodies derive from it
+    // is not shared by all twelve launch shapes ahead of the choice between
+    // them (which would not fit the registers).
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     run_if<16>(a.N, a, lds, g0 + q % ng, q / ng, tid);
-    if (--left == 0) break;
-    __syncthreads();  // the item's last LDS reads are done before the next item's loads land
   }
 
   // The last workgroup out clears the counters for the next launch.  (Thread

@@ -556,29 +556,28 @@ int record_batched(xeng_plan_t* p, const uint8_t* const* v, const int64_t* n_tim
     const int st = init_for_atomics(p, to_init);
     if (st != XENG_OK) return st;
   }
-  for (size_t first = 0; first < items.size(); first += xeng::batch::MAX_ARRAYS) {
+  for (size_t i = 0; i < items.size();) {
     xeng::batch::Params bp{};
     bp.counters = p->counters;
     int64_t n_items = 0;
-    const size_t last = std::min(items.size(), first + xeng::batch::MAX_ARRAYS);
-    for (size_t i = first; i < last; ++i) {
+    for (; i < items.size() && bp.n_arrays < xeng::batch::MAX_ARRAYS; ++i) {
       const BatchEntry& b = items[i];
       const ArrayState& s = p->arrays[b.a];
+      const int64_t more = (int64_t)b.ngroups * b.nchunks;
+      if (bp.n_arrays && n_items + more > xeng::batch::MAX_ITEMS) break;  // (the next launch's)
       const int k = bp.n_arrays++;
       bp.arr[k] = base_args(s, s.k, v[b.a], n_time[b.a]);
       bp.arr[k].t_chunk = b.t_chunk;
       bp.arr[k].mode = b.nchunks > 1 ? xeng::EPI_ATOMIC : (s.clean ? xeng::EPI_STORE : xeng::EPI_ADD);
       bp.ngroups[k] = b.ngroups;
       bp.nchunks[k] = b.nchunks;
-      n_items += (int64_t)b.ngroups * b.nchunks;
+      n_items += more;
     }
-    if (n_items > INT_MAX) return fail(p, XENG_EINVAL, "batch of %lld items", (long long)n_items);
-    bp.per_wg = 1;
+    if (n_items > xeng::batch::MAX_ITEMS) return fail(p, XENG_EINVAL, "array of %lld items", (long long)n_items);
     const int grid = (int)n_items;
     ++p->stats.launches;
     if (p->trace)
-      fprintf(stderr, "xeng: plan %p batch launch arrays=%d items=%lld grid=%d\n", (void*)p, bp.n_arrays,
-              (long long)n_items, grid);
+      fprintf(stderr, "xeng: plan %p batch launch arrays=%d items=%d\n", (void*)p, bp.n_arrays, grid);
     hipError_t e = xeng::batch::launch(grid, p->stream, bp);
     if (e != hipSuccess) return hip_fail(p, e, "batch kernel launch");
   }

@@ -89,3 +89,14 @@ def test_a_plan_is_made_where_the_accumulator_alone_fits():
     """)
     assert out[1:] == ["1", "1", "True True", "0"] and int(out[0]) > 2
     assert [m for _, _, m in launches(trace)] == [0, ATOMIC, ATOMIC]
+
+
+def test_a_batch_of_more_items_than_a_grid_holds():
+    """A grid holds fewer than 2^32 threads: 17 arrays of 2^20 channel groups
+    go in two launches."""
+    _, trace = run("""
+        h = X.xeng_plan([(16, (1 << 22) - 1, 1)] * 17)
+        call(h, [1] * 17)
+    """)
+    got = [tuple(int(x) for x in re.search(r"batch launch arrays=(\d+) items=(\d+)", l).groups()) for l in trace]
+    assert got == [(15, 15 << 20), (2, 2 << 20)]
