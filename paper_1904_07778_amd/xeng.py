@@ -334,7 +334,8 @@ def xeng_channelise_noalloc(adc, n_samples: int, n_inputs: int, n_chans: int, ou
 
 def channelise(adc, n_chans: int, out=None, tables=None, stream=None):
     """F-stage channeliser: int8 CUDA tensor [N, n_samples] of ADC samples ->
-    complex64 spectra [S, F, N] (time, channel, input)."""
+    complex64 spectra [S, F, N] (time, channel, input).  tables: the scratch
+    of xeng_channelise, checked but not needed."""
     import torch
     if adc.dim() != 2 or adc.dtype != torch.int8 or not adc.is_cuda or not adc.is_contiguous():
         raise ValueError("adc must be a contiguous int8 CUDA tensor [n_inputs, n_samples]")
@@ -344,11 +345,11 @@ def channelise(adc, n_chans: int, out=None, tables=None, stream=None):
         raise ValueError("bad sizes")
     if out is None:
         out = torch.empty((S, n_chans, N), dtype=torch.complex64, device=adc.device)
-    if tables is None:
-        tables = torch.empty(int(_lib.xeng_channelise_table_floats(n_chans)), dtype=torch.float32,
-                             device=adc.device)
     stream = stream if stream is not None else _current_stream()
-    xeng_channelise(adc, S_in, N, n_chans, out, tables, stream)
+    if tables is None:
+        xeng_channelise_noalloc(adc, S_in, N, n_chans, out, stream)
+    else:
+        xeng_channelise(adc, S_in, N, n_chans, out, tables, stream)
     return out
 
 
