@@ -91,8 +91,9 @@ enum {
  * The array indices of later calls are slots 0 .. n_arrays-1 (see
  * xeng_attach for more).  Allocates the HBM-resident int32 accumulators
  * (zeroed); a plain plan whose calls are split along time keeps room for the
- * chunks' sums beside them, up to 256 MB where that can be had.  Errors: EINVAL (null out, null arrays with n_arrays > 0, N or F
- * or max_time_per_call out of range, unknown flags), ENOMEM, EDEVICE.
+ * chunks' sums beside them, up to 256 MB where that can be had.  Errors:
+ * EINVAL (null out, null arrays with n_arrays > 0, N or F or
+ * max_time_per_call out of range, unknown flags), ENOMEM, EDEVICE.
  */
 int xeng_plan(xeng_plan_t **out, const xeng_array_desc *arrays, int32_t n_arrays,
               uint32_t flags, void *hip_stream);
@@ -224,8 +225,8 @@ int64_t xeng_accumulator_bytes(int32_t n_inputs, int32_t n_chans);
  * tile shape (16-row tiles of the 16x16x64 ring kernel, 32-row tiles of the
  * 32x32x32 ring kernel for N a multiple of 16, or 16-row tiles of the
  * staging kernel) and the number of workgroups per compute unit that the
- * time split aims for (0: the library's model of the call).  The choice is kept by the plan for later calls and
- * entered in the process's tuning cache (xeng_tune_cache_save), which new
+ * time split aims for (0: the library's model of the call).  The choice is
+ * kept by the plan for later calls and entered in the process's tuning cache (xeng_tune_cache_save), which new
  * plans of the same GPU architecture, kind, N and power-of-two buckets of F
  * and of max_time_per_call start from.  Every accumulator must be freshly
  * dumped (or never used); the trial sums are discarded and the accumulators

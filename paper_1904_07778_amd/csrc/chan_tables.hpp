@@ -16,8 +16,8 @@ namespace chan_math {
 
 constexpr double PI = 3.14159265358979323846;
 
-// sin and cos of x in [0, pi/4] by their Taylor series (the first term left
-// out is below 1e-19)
+// sin and cos of x in [0, pi/4] by their Taylor series (the first terms left
+// out, x^19 / 19! and x^18 / 18!, are below 1e-19 and 3e-18)
 constexpr double sin_small(double x) {
   double term = x, sum = x;
   for (int k = 1; k < 9; ++k) {

@@ -223,8 +223,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 // The compiler adds no wait states inside or in front of inline assembly, so
 // the ones that gfx950 needs stand in it: one between the write of M0 and the
 // load (s_nop 0), and five between a vector instruction that writes a
-// register of rsrc (v_readfirstlane) and the load.  The latter can only be
-// close before the first load of a stage (FIRST: s_nop 3).
+// register of rsrc (v_readfirstlane) and the load.  The latter is close only
+// before the first load of a stage (FIRST: s_nop 3); a CPU test measures both
+// distances in the built code.  N = 192, F = 1024, T = 8192: 466-478 us
+// without the waits, 471-473 with them.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 template <int OFF, bool FIRST>
@@ -401,8 +403,8 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
 
 // One work item: channel group `group` (channels CPW*group ..) over time
 // chunk `tchunk` (samples tchunk*t_chunk ..) of the call described by a.
-// tid is threadIdx.x (passed in so that a persistent caller can keep the
-// per-lane set-up from being hoisted out of its item loop).
+// tid is threadIdx.x (passed in so that the batch kernel can keep the per-lane
+// set-up of its launch shapes behind the choice between them).
 template <int N, int CPW, int S, int KPS, int LD, int WC>
 __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group, int tchunk, int tid) {
   using C = Shape<N, CPW, S, KPS, LD>;

@@ -270,8 +270,7 @@ __device__ __forceinline__ void epilogue(const Args& a, int f, int lane, const v
 
 // One work item: channel group `group` (channels CPW*group ..) over time
 // chunk `tchunk` (samples tchunk*t_chunk ..) of the call described by a.
-// tid is threadIdx.x (passed in so that a persistent caller can keep the
-// per-lane set-up from being hoisted out of its item loop).
+// tid is threadIdx.x.
 template <int N, int CPW, int S, int WC>
 __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group, int tchunk, int tid) {
   using C = Shape<N, CPW, S>;
