@@ -213,43 +213,58 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
-// One wave-wide 1 KB buffer load into LDS: lane i copies the 16 bytes at
-// rsrc.base + voff to LDS byte address lds_base + 16 i; offsets at or past
-// rsrc.num_records read as zero without touching memory.  Written as asm so
-// the compiler does not make every later LDS read wait for all loads in
-// flight (the ring waits for each stage with s_waitcnt vmcnt + barrier).
-// No register is written; M0 is otherwise unused by this code.
+// Wave-wide buffer loads into LDS: 1 KB where lane i copies the 16 bytes at
+// rsrc.base + voff to LDS byte address lds_base + OFF + 16 i (buf_dma<16>),
+// 256 bytes in dwords (buf_dma<4>); bytes at or past rsrc.num_records read as
+// zero without touching memory.  Written as asm so the compiler does not make
+// every later LDS read wait for all loads in flight (the ring waits for each
+// stage with s_waitcnt vmcnt + barrier).  No register is written; M0 is
+// otherwise unused by this code.
 //
 // The compiler adds no wait states inside or in front of inline assembly, so
 // the ones that gfx950 needs stand in it: one between the write of M0 and the
 // load (s_nop 0), and five between a vector instruction that writes a
 // register of rsrc (v_readfirstlane) and the load.  The latter is close only
 // before the first load of a stage (FIRST: s_nop 3); a CPU test measures both
-// distances in the built code.  N = 192, F = 1024, T = 8192: 466-478 us
-// without the waits, 471-473 with them.
+// distances in the built code.  Up to four loads to a block, STEP bytes of LDS
+// apart: between two blocks the compiler puts a wait state of its own, and a
+// load then takes 4 scalar instructions instead of 3 (N = 40, F = 1024, T =
+// 8192 70.2 us in blocks of one and 69.3 in these, N = 144, T = 4096 176 and
+// 174, N = 250 478 and 475, N = 192, T = 8192 480 and 479).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-template <int OFF, bool FIRST>
-__device__ __forceinline__ void buf_dma16(v4i rsrc, uint32_t voff, uint32_t lds_base) {
-  asm volatile(
-      "s_add_u32 m0, %2, %3\n\t"
-      "s_nop %4\n\t"
-      "buffer_load_dwordx4 %0, %1, 0 offen lds"
-      :
-      : "v"(voff), "s"(rsrc), "s"(lds_base), "i"(OFF), "i"(FIRST ? 3 : 0)
-      : "memory", "m0", "scc");
+#define XENG_DMA(op, v, off, nop) "s_add_u32 m0, %[base], %[" off "]\n\ts_nop " nop "\n\t" op " %[" v "], %[rsrc], 0 offen lds\n\t"
+#define XENG_DMA1(op) XENG_DMA(op, "v0", "o0", "%[n]")
+#define XENG_DMA2(op) XENG_DMA1(op) XENG_DMA(op, "v1", "o1", "0")
+#define XENG_DMA4(op) XENG_DMA2(op) XENG_DMA(op, "v2", "o2", "0") XENG_DMA(op, "v3", "o3", "0")
+#define XENG_DMA_IN1 [base] "s"(lds_base), [rsrc] "s"(rsrc), [n] "i"(FIRST ? 3 : 0), [v0] "v"(voff(K)), [o0] "i"(OFF)
+#define XENG_DMA_IN2 XENG_DMA_IN1, [v1] "v"(voff(K + 1)), [o1] "i"(OFF + STEP)
+#define XENG_DMA_IN4 \
+  XENG_DMA_IN2, [v2] "v"(voff(K + 2)), [o2] "i"(OFF + 2 * STEP), [v3] "v"(voff(K + 3)), [o3] "i"(OFF + 3 * STEP)
+// loads K .. COUNT - 1, voff(k) the byte offsets
+template <int BYTES, int OFF, int STEP, int COUNT, int K = 0, typename V>
+__device__ __forceinline__ void buf_dma(v4i rsrc, const V& voff, uint32_t lds_base) {
+  constexpr bool FIRST = K == 0;
+  constexpr int NOW = COUNT - K >= 4 ? 4 : COUNT - K >= 2 ? 2 : COUNT - K;
+  if constexpr (NOW == 4 && BYTES == 16)
+    asm volatile(XENG_DMA4("buffer_load_dwordx4") : : XENG_DMA_IN4 : "memory", "m0", "scc");
+  else if constexpr (NOW == 2 && BYTES == 16)
+    asm volatile(XENG_DMA2("buffer_load_dwordx4") : : XENG_DMA_IN2 : "memory", "m0", "scc");
+  else if constexpr (NOW == 1 && BYTES == 16)
+    asm volatile(XENG_DMA1("buffer_load_dwordx4") : : XENG_DMA_IN1 : "memory", "m0", "scc");
+  else if constexpr (NOW == 4)
+    asm volatile(XENG_DMA4("buffer_load_dword") : : XENG_DMA_IN4 : "memory", "m0", "scc");
+  else if constexpr (NOW > 0)
+    static_assert(NOW == 0, "dwords are loaded in whole blocks of four");
+  if constexpr (NOW > 0) x16::buf_dma<BYTES, OFF + NOW * STEP, STEP, COUNT, K + NOW>(rsrc, voff, lds_base);
 }
-// The same with 4 bytes per lane: a wave-wide 256-byte load.
-template <int OFF, bool FIRST>
-__device__ __forceinline__ void buf_dma4(v4i rsrc, uint32_t voff, uint32_t lds_base) {
-  asm volatile(
-      "s_add_u32 m0, %2, %3\n\t"
-      "s_nop %4\n\t"
-      "buffer_load_dword %0, %1, 0 offen lds"
-      :
-      : "v"(voff), "s"(rsrc), "s"(lds_base), "i"(OFF), "i"(FIRST ? 3 : 0)
-      : "memory", "m0", "scc");
-}
+#undef XENG_DMA
+#undef XENG_DMA1
+#undef XENG_DMA2
+#undef XENG_DMA4
+#undef XENG_DMA_IN1
+#undef XENG_DMA_IN2
+#undef XENG_DMA_IN4
 #pragma clang diagnostic pop
 
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
@@ -498,17 +513,18 @@ __device__ __forceinline__ void wave_main(const Args& a, uint8_t* lds, int group
     if constexpr (LD == LD_DWORD) {
       constexpr int ROW = C::RPP * 16;
       const uint32_t row0 = base + wave * (C::ROWS_PER_WAVE * ROW);
-      if (C::RPC * 4 == 64 || lane < C::RPC * 4) {
-        sfor<0, C::ROWS_PER_WAVE>(
-            [&](auto k) { buf_dma4<k * ROW, k == 0>(rsrc, voff[0] + (uint32_t)k * rs32, row0); });
-      }
-    } else if constexpr (ONE) {
-      sfor<0, LW>([&](auto k) { buf_dma16<(LR + k * NLW) * 1024, k == 0>(rsrc, voff[k], base); });
+      if (C::RPC * 4 == 64 || lane < C::RPC * 4)
+        buf_dma<4, 0, ROW, C::ROWS_PER_WAVE>(rsrc, [&](int k) { return voff[0] + (uint32_t)k * rs32; }, row0);
     } else {
-      const uint32_t q0 = base + wave * 1024;
-      sfor<0, LMAX>([&](auto k) {
-        if (k < my_loads) buf_dma16<k * C::WAVES * 1024, k == 0>(rsrc, voff[k], q0);
-      });
+      auto at = [&](int k) { return voff[k]; };
+      if constexpr (ONE) {
+        buf_dma<16, LR * 1024, NLW * 1024, LW>(rsrc, at, base);
+      } else {
+        const uint32_t q0 = base + wave * 1024;
+        buf_dma<16, 0, C::WAVES * 1024, C::LPW_MIN>(rsrc, at, q0);
+        if (C::LPW_MAX > C::LPW_MIN && my_loads == C::LPW_MAX)
+          buf_dma<16, C::LPW_MIN * C::WAVES * 1024, 0, C::LPW_MAX, C::LPW_MIN>(rsrc, at, q0);
+      }
     }
   };
 
